@@ -266,9 +266,12 @@ int sgemm_cube_compute_b(int64_t M, int64_t N, int64_t K, const float* B, int64_
  * tile column of C, so it is chosen only where that costs less than the
  * pass over A: A 16-byte aligned, lda a multiple of 4 and below 2^22, K a
  * multiple of 64, and the elementwise order with N <= 4096 and
- * scale <= 2^15, or the termwise order with N <= 2048 (any scale).  Enqueues nothing and reads no device
- * memory (A is only looked at as an address).  Both choices give the same
- * bits.
+ * scale <= 2^15, or the termwise order with N <= 2048 (any scale).  Problems
+ * whose 256-wide tiles would leave much of the GPU idle run on smaller tiles,
+ * which read planes: there A is split in the pass that splits B (compute_a: in
+ * a pass of a few microseconds) whatever this returns.  Enqueues nothing and
+ * reads no device memory (A is only looked at as an address).  Every choice
+ * gives the same bits.
  */
 int sgemm_cube_splits_a_in_gemm(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                                 float scale, int accum_order);

@@ -156,13 +156,24 @@ bool splits_a_in_gemm(int64_t N, const float* A, int64_t lda, int64_t K, float s
   return N <= max_n && fused_split_ok(A, lda, K, scale, variant);
 }
 
-// GEMM from FP32 A and a workspace whose B planes are prepared: the 256 x 256
-// kernel splits A in registers when splits_a_in_gemm says so, else A is split
+// Whether the GEMM of this problem runs on FP32 A: the rule above, where the
+// 256-wide kernels run.  The kernels of gemm_small.hip read planes only: at
+// their sizes the split of A is a few microseconds (none of its own where B is
+// split by the same call), while splitting A in their registers made them
+// slower by 1.2-5 us at 300 x 200 x 1024 to 1024^3 and by 12 us at
+// 48 x 4096 x 4096 (18 to 30 us).
+bool gemm_reads_fp32_a(int64_t M, int64_t N, const float* A, int64_t lda, int64_t K, float scale,
+                       int variant) {
+  return splits_a_in_gemm(N, A, lda, K, scale, variant) && small_gemm_tile(M, N, variant) == 0;
+}
+
+// GEMM from FP32 A and a workspace whose B planes are prepared: the 256-wide
+// kernel splits A in registers when gemm_reads_fp32_a says so, else A is split
 // into the workspace first and the GEMM runs on the planes.
 hipError_t compute_from_a(const Planes& p, int64_t M, int64_t N, int64_t K, const float* A,
                           int64_t lda, float* C, int64_t ldc, float scale, int variant,
                           hipStream_t stream) {
-  if (splits_a_in_gemm(N, A, lda, K, scale, variant))
+  if (gemm_reads_fp32_a(M, N, A, lda, K, scale, variant))
     return launch_gemm_fused_a(p, M, N, K, A, lda, C, ldc, scale, variant, stream);
   const hipError_t e = launch_split_a(p, M, K, A, lda, scale, RangeOpts{}, next_stamp(), stream);
   if (e != hipSuccess) return e;
@@ -195,7 +206,7 @@ int run(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const floa
                ? SGEMM_CUBE_OK
                : SGEMM_CUBE_ERR_HIP;
   }
-  if (!opt.prescale && !opt.report && splits_a_in_gemm(N, A, lda, K, scale, variant)) {
+  if (!opt.prescale && !opt.report && gemm_reads_fp32_a(M, N, A, lda, K, scale, variant)) {
     // B is split into the workspace, A inside the GEMM kernel.
     if (launch_split_b(p, K, N, B, ldb, scale, opt, next_stamp(), stream) != hipSuccess)
       return SGEMM_CUBE_ERR_HIP;

@@ -162,7 +162,20 @@ hipError_t launch_unscale(const Planes& p, int64_t M, int64_t N, float* C, int64
 // (0 when `empty`, i.e. no split ran).
 hipError_t launch_range_report(const Planes& p, bool empty, uint32_t* out, hipStream_t stream);
 
-// Enqueue the MFMA GEMM on prepared planes.
+// Tile side (32, 64 or 128) of the kernel in gemm_small.hip that runs an
+// M x N problem in the order `variant`, or 0 for the 256-wide kernels.
+int small_gemm_tile(int64_t M, int64_t N, int variant);
+
+// The GEMM on tile x tile tiles (gemm_small.hip).  Same results as the 256-wide
+// kernels, bit for bit, range fallbacks included.
+hipError_t launch_gemm_small(int tile, const Planes& p, int64_t M, int64_t N, float* C,
+                             int64_t ldc, float scale, int variant, hipStream_t stream);
+
+// The 256-wide kernels (gemm.hip) on prepared planes.
+hipError_t launch_gemm_wide(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,
+                            float scale, int variant, hipStream_t stream);
+
+// Enqueue the MFMA GEMM on prepared planes, on the tile small_gemm_tile picks.
 hipError_t launch_gemm(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,
                        float scale, int variant, hipStream_t stream);
 

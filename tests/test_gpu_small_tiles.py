@@ -1,0 +1,84 @@
+"""The 32, 64 and 128-wide tile kernels that the library picks for problems
+whose 256-wide tiles leave compute units idle, at tile edges and remainders.
+
+Elementwise: bit for bit the 256 x 256 sweep kernel on the same planes (scaled
+body, range fallback, s > 2^15).  Termwise: bit for bit the 256 x 128 kernel
+that splits B itself.  Cross-terms-first (both bodies) and the FP16 baseline:
+the oracle, within the bar 2 K 2^-24 |A||B|."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from tests.gpu_util import gemm, hgemm, log, to_dev
+from tests.helpers import abs_ab, assert_parity, band_rows
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K): the tile a shape takes depends on M and N alone.  One tile with
+# remainders, a full grid of 32-wide tiles, 64-wide, 128-wide (one tile less
+# than full in each dimension); K of one, three and eleven steps of 64.
+SHAPES = [(31, 36, 64), (257, 260, 192), (512, 512, 64), (700, 1020, 192), (1100, 1500, 704)]
+
+
+@pytest.mark.parametrize("overflow,scale", [(False, 2048.0), (True, 2048.0), (False, 65536.0)],
+                         ids=["scaled", "range", "large_scale"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_elementwise_gives_the_wide_kernels_bits(gpu, shape, overflow, scale):
+    import torch
+
+    from paper_2507_23387_amd import binding
+
+    M, N, K = shape
+    A, B = workloads.make_operands(M, N, K, M + K, "normal")
+    if overflow:
+        B[K - 1, N - 1] = np.float32(40.0)
+    log(f"small tiles elementwise {M}x{N}x{K} overflow={overflow} s={scale}")
+    dA, dB = to_dev(A), to_dev(B)
+    ws = binding.workspace(M, N, K)
+    st = torch.cuda.current_stream().cuda_stream
+    assert binding.sgemm_cube_prepare(M, N, K, dA.data_ptr(), K, dB.data_ptr(), N, scale,
+                                      ws.data_ptr(), ws.numel(), st) == 0
+    C = [torch.full((M, N), float("nan"), device="cuda") for _ in range(3)]
+    assert binding.sgemm_cube_compute(M, N, K, C[0].data_ptr(), N, scale, 0, ws.data_ptr(),
+                                      ws.numel(), st) == 0
+    assert binding.sgemm_cube_compute_tile(M, N, K, C[1].data_ptr(), N, scale, 0, 256, 256, 32, 4,
+                                           ws.data_ptr(), ws.numel(), st) == 0
+    assert binding.sgemm_cube_ws(M, N, K, dA.data_ptr(), K, dB.data_ptr(), N, C[2].data_ptr(), N,
+                                 scale, 0, ws.data_ptr(), ws.numel(), st) == 0
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(C[0]).all())
+    for other in C[1:]:
+        assert torch.equal(C[0].view(torch.int32), other.view(torch.int32))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_termwise_gives_the_wide_kernels_bits(gpu, shape):
+    import torch
+
+    from paper_2507_23387_amd import binding
+
+    M, N, K = shape
+    A, B = workloads.make_operands(M, N, K, M + K, "normal")
+    log(f"small tiles termwise {M}x{N}x{K}")
+    dA, dB = to_dev(A), to_dev(B)
+    got = binding.matmul(dA, dB, order="termwise")
+    wide = binding.matmul_ex(dA, dB, order="termwise", split_b_in_gemm=True)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int32), wide.view(torch.int32))
+
+
+@pytest.mark.parametrize("kind", ["cross", "cross_range", "hgemm"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_cross_first_and_baseline_against_the_oracle(gpu, shape, kind):
+    M, N, K = shape
+    A, B = workloads.make_operands(M, N, K, M + K, "normal")
+    if kind == "cross_range":
+        B[0, 0] = np.float32(40.0)
+    log(f"small tiles {kind} {M}x{N}x{K}")
+    C = hgemm(A, B) if kind == "hgemm" else gemm(A, B, 2048.0, "elementwise_cross_first")
+    assert np.isfinite(C).all()
+    rows = band_rows(M, K, band=16)
+    order = "hi_only" if kind == "hgemm" else "elementwise_cross_first"
+    want = oracle.sgemm_rows(A, B, rows, 2048.0, order, kb=32)
+    assert_parity(C[rows], want, K, abs_ab(A, B, rows), f"small tiles {kind} {shape}")
