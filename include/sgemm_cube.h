@@ -268,10 +268,11 @@ int sgemm_cube_compute_b(int64_t M, int64_t N, int64_t K, const float* B, int64_
  * multiple of 64, and the elementwise order with N <= 4096 and
  * scale <= 2^15, or the termwise order with N <= 2048 (any scale).  Problems
  * whose 256-wide tiles would leave much of the GPU idle run on smaller tiles,
- * which read planes: there A is split in the pass that splits B (compute_a: in
- * a pass of a few microseconds) whatever this returns.  Enqueues nothing and
- * reads no device memory (A is only looked at as an address).  Every choice
- * gives the same bits.
+ * which read planes: there, and in the elementwise order above N = 3072, A is
+ * split in the pass that splits B (compute_a: in a pass of its own) whatever
+ * this returns, which measured as fast or faster.  Enqueues nothing and reads
+ * no device memory (A is only looked at as an address).  Every choice gives
+ * the same bits.
  */
 int sgemm_cube_splits_a_in_gemm(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                                 float scale, int accum_order);

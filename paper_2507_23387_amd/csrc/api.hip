@@ -76,8 +76,8 @@ bool overlap(const void* p, uint64_t pn, const void* q, uint64_t qn) {
   return a < b + qn && b < a + pn;
 }
 
-// Grid limits: GEMM workgroups (at most (Mp / 256) * (Np / 128)) must fit an
-// int, and the split of B uses grid.y = Np / 128 <= 65535.
+// Grid limits: GEMM workgroups (at most (Mp / 256) * (Np / 128) of the wide
+// kernels) must fit an int, and B has at most 65535 panels (Np / 128).
 bool round_up_tiles_exceed(int64_t M, int64_t N) {
   const int64_t Mp = round_up(M, kRowPad), Np = round_up(N, kRowPad);
   return (Mp / 256) * (Np / 128) > INT32_MAX || Np / kPanel > 65535;
@@ -105,7 +105,7 @@ int validate_gemm(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, 
   return SGEMM_CUBE_OK;
 }
 
-// A fresh stamp for every split of B (see launch_split_b); 0 is skipped.
+// A fresh stamp for every split of an operand (see launch_split); 0 is skipped.
 std::atomic<uint32_t> g_stamp{0};
 uint32_t next_stamp() {
   uint32_t s = g_stamp.fetch_add(1, std::memory_order_relaxed) + 1;
@@ -147,6 +147,7 @@ RangeOpts range_opts(unsigned options, bool report, float scale) {
 // x 16384, so it is used up to N = 2048.
 constexpr int64_t kFusedSplitMaxN = 4096;
 constexpr int64_t kTermwiseFusedMaxN = 2048;
+constexpr int64_t kWideFusedMaxN = 3072;
 
 bool splits_a_in_gemm(int64_t N, const float* A, int64_t lda, int64_t K, float scale,
                       int variant) {
@@ -157,14 +158,20 @@ bool splits_a_in_gemm(int64_t N, const float* A, int64_t lda, int64_t K, float s
 }
 
 // Whether the GEMM of this problem runs on FP32 A: the rule above, where the
-// 256-wide kernels run.  The kernels of gemm_small.hip read planes only: at
+// 256-wide kernels run and, elementwise, N <= 3072: with both operands split by
+// one launch the planes are as fast at N = 4096 (4096^3: 312 us against 316,
+// 4096 x 4096 x 16384: 1197 against 1195; 8192 x 3072 x 4096: 534 against 526),
+// and when the range flag is set the plane path has its planes already, which
+// the fused kernel would first write at half a split pass's rate (4096 x 4096 x
+// 16384: 157 us against 94).  The kernels of gemm_small.hip read planes only: at
 // their sizes the split of A is a few microseconds (none of its own where B is
 // split by the same call), while splitting A in their registers made them
 // slower by 1.2-5 us at 300 x 200 x 1024 to 1024^3 and by 12 us at
 // 48 x 4096 x 4096 (18 to 30 us).
 bool gemm_reads_fp32_a(int64_t M, int64_t N, const float* A, int64_t lda, int64_t K, float scale,
                        int variant) {
-  return splits_a_in_gemm(N, A, lda, K, scale, variant) && small_gemm_tile(M, N, variant) == 0;
+  return splits_a_in_gemm(N, A, lda, K, scale, variant) && N <= kWideFusedMaxN &&
+         small_gemm_tile(M, N, variant) == 0;
 }
 
 // GEMM from FP32 A and a workspace whose B planes are prepared: the 256-wide
@@ -175,7 +182,8 @@ hipError_t compute_from_a(const Planes& p, int64_t M, int64_t N, int64_t K, cons
                           hipStream_t stream) {
   if (gemm_reads_fp32_a(M, N, A, lda, K, scale, variant))
     return launch_gemm_fused_a(p, M, N, K, A, lda, C, ldc, scale, variant, stream);
-  const hipError_t e = launch_split_a(p, M, K, A, lda, scale, RangeOpts{}, next_stamp(), stream);
+  const hipError_t e = launch_split(p, M, N, K, A, lda, nullptr, 0, scale, RangeOpts{},
+                                    next_stamp(), 0, kSplitRows, stream);
   if (e != hipSuccess) return e;
   return launch_gemm(p, M, N, C, ldc, scale, variant, stream);
 }
@@ -199,7 +207,8 @@ int run(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const floa
     // A too where the library splits it there, else by its own pass.
     const bool fused_a = splits_a_in_gemm(N, A, lda, K, scale, variant);
     if (!fused_a &&
-        launch_split_a(p, M, K, A, lda, scale, opt, next_stamp(), stream) != hipSuccess)
+        launch_split(p, M, N, K, A, lda, nullptr, 0, scale, opt, next_stamp(), 0, kSplitRows,
+                     stream) != hipSuccess)
       return SGEMM_CUBE_ERR_HIP;
     return launch_gemm_fused_b(p, M, N, K, A, lda, fused_a, B, ldb, C, ldc, scale, stream) ==
                    hipSuccess
@@ -208,7 +217,8 @@ int run(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const floa
   }
   if (!opt.prescale && !opt.report && gemm_reads_fp32_a(M, N, A, lda, K, scale, variant)) {
     // B is split into the workspace, A inside the GEMM kernel.
-    if (launch_split_b(p, K, N, B, ldb, scale, opt, next_stamp(), stream) != hipSuccess)
+    if (launch_split(p, M, N, K, nullptr, 0, B, ldb, scale, opt, 0, next_stamp(), kSplitRows,
+                     stream) != hipSuccess)
       return SGEMM_CUBE_ERR_HIP;
     return compute_from_a(p, M, N, K, A, lda, C, ldc, scale, variant, stream) == hipSuccess
                ? SGEMM_CUBE_OK
@@ -216,9 +226,9 @@ int run(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const floa
   }
   if (opt.prescale && launch_absmax(p, M, N, K, A, lda, B, ldb, stream) != hipSuccess)
     return SGEMM_CUBE_ERR_HIP;
-  if (launch_split_a(p, M, K, A, lda, scale, opt, next_stamp(), stream) != hipSuccess)
-    return SGEMM_CUBE_ERR_HIP;
-  if (launch_split_b(p, K, N, B, ldb, scale, opt, next_stamp(), stream) != hipSuccess)
+  const uint32_t a_stamp = next_stamp(), b_stamp = next_stamp();
+  if (launch_split(p, M, N, K, A, lda, B, ldb, scale, opt, a_stamp, b_stamp,
+                   variant == kHiOnly ? kSplitHigh : kSplitRows, stream) != hipSuccess)
     return SGEMM_CUBE_ERR_HIP;
   if (launch_gemm(p, M, N, C, ldc, scale, variant, stream) != hipSuccess)
     return SGEMM_CUBE_ERR_HIP;
@@ -454,14 +464,12 @@ int sgemm_cube_prepare(int64_t M, int64_t N, int64_t K, const float* A, int64_t 
     return SGEMM_CUBE_ERR_INVALID_VALUE;
   if (sgc::round_up_tiles_exceed(M, N)) return SGEMM_CUBE_ERR_NOT_SUPPORTED;
   const sgc::Planes p = sgc::plan_planes(M, N, K, ws);
-  const sgc::RangeOpts plain;
-  if (A && sgc::launch_split_a(p, M, K, A, lda, scale, plain, sgc::next_stamp(), stream) !=
-               hipSuccess)
-    return SGEMM_CUBE_ERR_HIP;
-  if (B && sgc::launch_split_b(p, K, N, B, ldb, scale, plain, sgc::next_stamp(), stream) !=
-               hipSuccess)
-    return SGEMM_CUBE_ERR_HIP;
-  return SGEMM_CUBE_OK;
+  if (!A && !B) return SGEMM_CUBE_OK;
+  const uint32_t a_stamp = sgc::next_stamp(), b_stamp = sgc::next_stamp();
+  return sgc::launch_split(p, M, N, K, A, lda, B, ldb, scale, sgc::RangeOpts{}, a_stamp, b_stamp,
+                           sgc::kSplitPadded, stream) == hipSuccess
+             ? SGEMM_CUBE_OK
+             : SGEMM_CUBE_ERR_HIP;
 }
 
 int sgemm_cube_compute(int64_t M, int64_t N, int64_t K, float* C, int64_t ldc, float scale,
@@ -587,8 +595,6 @@ int sgemm_cube_hgemm(int64_t M, int64_t N, int64_t K, const float* A, int64_t ld
                      const float* B, int64_t ldb, float* C, int64_t ldc, hipStream_t stream) {
   const int st = sgc::validate_gemm(M, N, K, A, lda, B, ldb, C, ldc, 1.0f, false);
   if (st != SGEMM_CUBE_OK) return st;
-  // The hi-only baseline does not read the residual planes; the split still
-  // fills them so the whole split pass is shared.
   return sgc::run_allocating(M, N, K, A, lda, B, ldb, C, ldc, 1.0f, sgc::kHiOnly, stream);
 }
 

@@ -133,20 +133,24 @@ hipError_t launch_split_rows(int64_t rows, int64_t cols, const float* X, int64_t
                              uint16_t* hi, uint16_t* lo, int64_t ldh, float scale,
                              hipStream_t stream);
 
-// Enqueue the split of A (M x K row-major) into the tiled A planes,
-// zero-filling the padding up to Mp x Kp; with opt.prescale row i is first
-// multiplied by its power of two (p.row_max), with opt.report the range
-// classes are stamped (`stamp`) into the workspace header.
-hipError_t launch_split_a(const Planes& p, int64_t M, int64_t K, const float* A, int64_t lda,
-                          float scale, const RangeOpts& opt, uint32_t stamp, hipStream_t stream);
+// What a split writes: both planes of the operands' own rows (the padding rows
+// of the planes, which only feed entries that are never stored, are left
+// alone), both planes with the padding rows zeroed (planes that outlive the
+// call), or the high planes alone (the FP16 baseline).  The padding of K is
+// always zeroed.
+enum SplitPlanes { kSplitRows, kSplitPadded, kSplitHigh };
 
-// Enqueue the split of B (K x N row-major) into the tiled, transposed B
-// planes (Np x Kp), zero-filling the padding, and recompute the range flag.
-// `stamp` must differ from the stamp of the previous split into the same
-// workspace (the C-ABI draws a fresh one per call).
-hipError_t launch_split_b(const Planes& p, int64_t K, int64_t N, const float* B, int64_t ldb,
-                          float scale, const RangeOpts& opt, uint32_t stamp,
-                          hipStream_t stream);
+// Enqueue, in one launch, the split of A (M x K row-major) into the tiled A
+// planes (A null: none) and of B (K x N row-major) into the tiled, transposed B
+// planes with the range flag (B null: none).  With opt.prescale row i of A
+// (column j of B) is first multiplied by its power of two (p.row_max,
+// p.col_max), with opt.report the range classes are stamped into the workspace
+// header.  Each operand's stamp must differ from that of the previous split
+// into the same workspace (the C-ABI draws fresh ones per call).
+hipError_t launch_split(const Planes& p, int64_t M, int64_t N, int64_t K, const float* A,
+                        int64_t lda, const float* B, int64_t ldb, float scale,
+                        const RangeOpts& opt, uint32_t a_stamp, uint32_t b_stamp, SplitPlanes what,
+                        hipStream_t stream);
 
 // Pre-scaling: enqueue the row maxima of |A| and column maxima of |B| (finite
 // entries only) into p.row_max / p.col_max.
@@ -210,7 +214,7 @@ hipError_t launch_gemm_tile(const Planes& p, int64_t M, int64_t N, float* C, int
 bool fused_split_ok(const float* A, int64_t lda, int64_t K, float scale, int variant);
 
 // GEMM that reads A as FP32 and splits it in registers, on a workspace whose B
-// planes (and range flag) were written by launch_split_b; requires
+// planes (and range flag) were written by launch_split; requires
 // fused_split_ok.  Elementwise: the 256 x 256 kernel; when the range flag is
 // set (some |B_hi| s > 65504) it writes the A planes instead and the unscaled
 // elementwise kernel, launched after it, computes C.  Termwise: the 256 x 128

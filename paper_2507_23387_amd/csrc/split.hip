@@ -12,6 +12,8 @@
 //     by the C-ABI), so this equals the two-step definition bit for bit.
 // All split kernels are HBM-bound elementwise passes: 4 B read and 4 B
 // written (hi + lo) per element.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace sgc {
@@ -86,99 +88,133 @@ __device__ __forceinline__ void report_classes(uint32_t cls, uint32_t* range, in
   }
 }
 
-// Split of A into the tiled planes.  A workgroup covers 16 rows x 128 k and a
-// wave 4 rows x 128 k: lane l takes 8 consecutive k of row l / 16, so each row
-// is read as one 512-byte piece, and the 16-byte chunks a store instruction
-// writes fill 8 whole 128-byte lines (4 rows x 32 bytes of one tile each).
-// blockIdx.y strides over row blocks.
-template <bool kVec, bool kPre, bool kReport>
-__global__ __launch_bounds__(256) void split_a_tiled_kernel(
-    int64_t M, int64_t K, const float* __restrict__ X, int64_t ldx, uint16_t* __restrict__ hi,
-    uint16_t* __restrict__ lo, int64_t Mp, int64_t Kp, float s,
-    const uint32_t* __restrict__ row_max, int exp_a, uint32_t* __restrict__ range,
-    uint32_t stamp) {
+// Four consecutive floats at any 4-byte aligned address: one 16-byte load (the
+// hardware takes any dword alignment), so rows of any leading dimension are
+// read as whole pieces.
+typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ void load8(const float* src, float (&v)[8]) {
+  const floatx4_u f0 = *reinterpret_cast<const floatx4_u*>(src);
+  const floatx4_u f1 = *reinterpret_cast<const floatx4_u*>(src + 4);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = f0[e];
+    v[e + 4] = f1[e];
+  }
+}
+
+// Both operands of one split launch, cut into blocks of kABlockRows rows x 128
+// k of A and 32 k x 128 n of B; the A blocks come first.
+constexpr int kABlockRows = 32;
+struct SplitArgs {
+  float s;
+  uint32_t* range;
+  int64_t Kp;
+  uint32_t a_blocks, blocks;  // of A, of both (32-bit: the kernel divides them)
+  // A
+  const float* A;
+  int64_t lda, M, K;
+  uint16_t* a_hi;
+  uint16_t* a_lo;
+  const uint32_t* row_max;
+  int exp_a;
+  uint32_t a_stamp;
+  // B
+  const float* B;
+  int64_t ldb, N;
+  uint16_t* b_hi;
+  uint16_t* b_lo;
+  const uint32_t* col_max;
+  int exp_b;
+  uint32_t b_stamp;
+};
+
+// A block of A into the tiled planes: a wave takes 2 x 4 rows x 128 k, lane l 8
+// consecutive k of rows l / 16 and l / 16 + 16, so each row is read as one
+// 512-byte piece, and the 16-byte chunks a store instruction writes fill 8
+// whole 128-byte lines (4 rows x 32 bytes of one tile each).
+template <bool kPre, bool kReport, bool kLo>
+__device__ __forceinline__ void split_a_block(const SplitArgs& g, uint32_t block) {
   const int lane = threadIdx.x & 63;
-  const int64_t k0 = static_cast<int64_t>(blockIdx.x) * 128 + (lane & 15) * 8;
-  if (kReport && threadIdx.x == 0) range[kWordAStamp] = stamp;
-  if (k0 >= Kp) return;
-  uint32_t cls = 0;
-  for (int64_t m = static_cast<int64_t>(blockIdx.y) * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4);
-       m < Mp; m += static_cast<int64_t>(gridDim.y) * 16) {
-    float v[8];
-    if (kVec && m < M && k0 + 7 < K) {
-      const float4* src = reinterpret_cast<const float4*>(X + m * ldx + k0);
-      const float4 f0 = src[0], f1 = src[1];
-      v[0] = f0.x; v[1] = f0.y; v[2] = f0.z; v[3] = f0.w;
-      v[4] = f1.x; v[5] = f1.y; v[6] = f1.z; v[7] = f1.w;
+  const uint32_t kblocks = static_cast<uint32_t>((g.Kp + 127) / 128);
+  const uint32_t rows = block / kblocks;
+  const int64_t k0 = static_cast<int64_t>(block - rows * kblocks) * 128 + (lane & 15) * 8;
+  const int64_t m0 = static_cast<int64_t>(rows) * kABlockRows + (threadIdx.x >> 6) * 4 + (lane >> 4);
+  if (kReport && threadIdx.x == 0) g.range[kWordAStamp] = g.a_stamp;
+  if (k0 >= g.Kp) return;
+  float v[kABlockRows / 16][8];
+#pragma unroll
+  for (int u = 0; u < kABlockRows / 16; ++u) {
+    const int64_t m = m0 + 16 * u;
+    if (m < g.M && k0 + 7 < g.K) {
+      load8(g.A + m * g.lda + k0, v[u]);
     } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = (m < M && k0 + e < K) ? X[m * ldx + k0 + e] : 0.0f;
+      for (int e = 0; e < 8; ++e)
+        v[u][e] = (m < g.M && k0 + e < g.K) ? g.A[m * g.lda + k0 + e] : 0.0f;
     }
-    if constexpr (kPre) {
-      const int shift = m < M ? prescale_shift(row_max[m], exp_a) : 0;
+  }
+  uint32_t cls = 0;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = __builtin_ldexpf(v[e], shift);
+  for (int u = 0; u < kABlockRows / 16; ++u) {
+    const int64_t m = m0 + 16 * u;
+    if constexpr (kPre) {
+      const int shift = m < g.M ? prescale_shift(g.row_max[m], g.exp_a) : 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[u][e] = __builtin_ldexpf(v[u][e], shift);
     }
     u32x4 hv, lv;
-    split8(v, s, hv, lv);
+    split8(v[u], g.s, hv, lv);
     if constexpr (kReport) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        cls |= range_class(v[2 * e], hv[e] & 0xffff, lv[e] & 0xffff);
-        cls |= range_class(v[2 * e + 1], hv[e] >> 16, lv[e] >> 16);
+        cls |= range_class(v[u][2 * e], hv[e] & 0xffff, lv[e] & 0xffff);
+        cls |= range_class(v[u][2 * e + 1], hv[e] >> 16, lv[e] >> 16);
       }
     }
-    const int64_t idx = tiled_index(m, k0, Kp);
-    store_stream(hi + idx, hv);
-    store_stream(lo + idx, lv);
+    const int64_t idx = tiled_index(m, k0, g.Kp);
+    store_stream(g.a_hi + idx, hv);
+    if constexpr (kLo) store_stream(g.a_lo + idx, lv);
   }
-  if constexpr (kReport) report_classes(cls, range, kWordAClass, stamp);
+  if constexpr (kReport) report_classes(cls, g.range, kWordAClass, g.a_stamp);
 }
 
-// Split of B (K x N row-major) into the tiled planes of B transposed.  One
-// workgroup = 32 k x 128 n (two tiles): thread t splits rows k and k+1
-// (k = 2 (t / 16)) at 8 consecutive n, each wave reading eight 512-byte row
-// pieces.  The (k, k+1) pairs of hi and of lo go to LDS as 32-bit words, n-major,
-// so each 16-byte chunk of a tile row is one LDS read; thread t then writes
-// chunk t of both tiles of both planes (4 KiB contiguous per tile).  It also
-// stamps the range flag (see launch_split_b) when some |B_hi| s > 65504, the
-// largest finite FP16 value.
-template <bool kVec, bool kPre, bool kReport>
-__global__ __launch_bounds__(256) void split_b_tiled_kernel(
-    int64_t K, int64_t N, const float* __restrict__ B, int64_t ldb, uint16_t* __restrict__ hi,
-    uint16_t* __restrict__ lo, int64_t Kp, float s, const uint32_t* __restrict__ col_max,
-    int exp_b, uint32_t* __restrict__ range, uint32_t stamp) {
+// A block of B into the tiled planes of B transposed (two tiles): thread t
+// splits rows k and k+1 (k = 2 (t / 16)) at 8 consecutive n, each wave reading
+// eight 512-byte row pieces.  The (k, k+1) pairs of hi and of lo go to LDS as
+// 32-bit words, n-major, so each 16-byte chunk of a tile row is one LDS read;
+// thread t then writes chunk t of both tiles of both planes (4 KiB contiguous
+// per tile).  It also stamps the range flag (see launch_split) when some
+// |B_hi| s > 65504, the largest finite FP16 value.
+template <bool kPre, bool kReport, bool kLo>
+__device__ __forceinline__ void split_b_block(const SplitArgs& g, uint32_t block) {
   constexpr int kK = 2 * kSlice;
   constexpr int kPitch = kK / 2 + 4;  // words per n row; 16-byte aligned rows
   __shared__ __align__(16) uint32_t ph[kPanel * kPitch];
-  __shared__ __align__(16) uint32_t pl[kPanel * kPitch];
+  __shared__ __align__(16) uint32_t pl[kLo ? kPanel * kPitch : 4];
   const int t = threadIdx.x;
-  const int64_t kblock = blockIdx.x;
-  const int64_t panel = blockIdx.y;
+  const uint32_t kblocks = static_cast<uint32_t>(g.Kp / kK);
+  const int64_t panel = block / kblocks;
+  const int64_t kblock = block - static_cast<uint32_t>(panel) * kblocks;
   const int nl = (t & 15) * 8;
   const int kp = t >> 4;  // k pair
   const int64_t k = kblock * kK + 2 * kp;
   const int64_t n = panel * kPanel + nl;
   float v0[8], v1[8];
-  if (kVec && k + 1 < K && n + 7 < N) {
-    const float4* r0 = reinterpret_cast<const float4*>(B + k * ldb + n);
-    const float4* r1 = reinterpret_cast<const float4*>(B + (k + 1) * ldb + n);
-    const float4 a0 = r0[0], a1 = r0[1], c0 = r1[0], c1 = r1[1];
-    v0[0] = a0.x; v0[1] = a0.y; v0[2] = a0.z; v0[3] = a0.w;
-    v0[4] = a1.x; v0[5] = a1.y; v0[6] = a1.z; v0[7] = a1.w;
-    v1[0] = c0.x; v1[1] = c0.y; v1[2] = c0.z; v1[3] = c0.w;
-    v1[4] = c1.x; v1[5] = c1.y; v1[6] = c1.z; v1[7] = c1.w;
+  if (k + 1 < g.K && n + 7 < g.N) {
+    load8(g.B + k * g.ldb + n, v0);
+    load8(g.B + (k + 1) * g.ldb + n, v1);
   } else {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      v0[e] = (k < K && n + e < N) ? B[k * ldb + n + e] : 0.0f;
-      v1[e] = (k + 1 < K && n + e < N) ? B[(k + 1) * ldb + n + e] : 0.0f;
+      v0[e] = (k < g.K && n + e < g.N) ? g.B[k * g.ldb + n + e] : 0.0f;
+      v1[e] = (k + 1 < g.K && n + e < g.N) ? g.B[(k + 1) * g.ldb + n + e] : 0.0f;
     }
   }
   if constexpr (kPre) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int shift = n + e < N ? prescale_shift(col_max[n + e], exp_b) : 0;
+      const int shift = n + e < g.N ? prescale_shift(g.col_max[n + e], g.exp_b) : 0;
       v0[e] = __builtin_ldexpf(v0[e], shift);
       v1[e] = __builtin_ldexpf(v1[e], shift);
     }
@@ -188,27 +224,42 @@ __global__ __launch_bounds__(256) void split_b_tiled_kernel(
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     uint16_t h0, l0, h1, l1;
-    split_value(v0[e], s, h0, l0);
-    split_value(v1[e], s, h1, l1);
-    big |= __builtin_fabsf(static_cast<float>(__builtin_bit_cast(_Float16, h0))) * s > 65504.0f;
-    big |= __builtin_fabsf(static_cast<float>(__builtin_bit_cast(_Float16, h1))) * s > 65504.0f;
+    split_value(v0[e], g.s, h0, l0);
+    split_value(v1[e], g.s, h1, l1);
+    big |= __builtin_fabsf(static_cast<float>(__builtin_bit_cast(_Float16, h0))) * g.s > 65504.0f;
+    big |= __builtin_fabsf(static_cast<float>(__builtin_bit_cast(_Float16, h1))) * g.s > 65504.0f;
     if constexpr (kReport) cls |= range_class(v0[e], h0, l0) | range_class(v1[e], h1, l1);
     ph[(nl + e) * kPitch + kp] = static_cast<uint32_t>(h0) | (static_cast<uint32_t>(h1) << 16);
-    pl[(nl + e) * kPitch + kp] = static_cast<uint32_t>(l0) | (static_cast<uint32_t>(l1) << 16);
+    if constexpr (kLo)
+      pl[(nl + e) * kPitch + kp] = static_cast<uint32_t>(l0) | (static_cast<uint32_t>(l1) << 16);
   }
-  if (big) range[kWordBOverflow] = stamp;
-  if (t == 0) range[kWordBStamp] = stamp;
-  if constexpr (kReport) report_classes(cls, range, kWordBClass, stamp);
+  if (big) g.range[kWordBOverflow] = g.b_stamp;
+  if (t == 0) g.range[kWordBStamp] = g.b_stamp;
+  if constexpr (kReport) report_classes(cls, g.range, kWordBClass, g.b_stamp);
   __syncthreads();
   const int r = t >> 1;
   const int c = (t & 1) ^ tile_swizzle(r);  // logical chunk stored at position t & 1
 #pragma unroll
   for (int sl = 0; sl < kK / kSlice; ++sl) {
-    const u32x4 hv = *reinterpret_cast<const u32x4*>(ph + r * kPitch + sl * 8 + c * 4);
-    const u32x4 lv = *reinterpret_cast<const u32x4*>(pl + r * kPitch + sl * 8 + c * 4);
-    const int64_t base = (panel * (Kp / kSlice) + kblock * (kK / kSlice) + sl) * kTileHalves + t * 8;
-    store_stream(hi + base, hv);
-    store_stream(lo + base, lv);
+    const int64_t base = (panel * (g.Kp / kSlice) + kblock * (kK / kSlice) + sl) * kTileHalves + t * 8;
+    store_stream(g.b_hi + base, *reinterpret_cast<const u32x4*>(ph + r * kPitch + sl * 8 + c * 4));
+    if constexpr (kLo)
+      store_stream(g.b_lo + base, *reinterpret_cast<const u32x4*>(pl + r * kPitch + sl * 8 + c * 4));
+  }
+}
+
+// The split of A, of B or of both in one launch.  HBM-bound at size (8192^3: 187
+// us for 1 GiB moved, 5.7 TB/s; 192 us as two launches; B's blocks first 197);
+// below about 10 MB a launch, 4 us, is all it costs, hence one for both
+// operands (256^3: 8.7 to 5.0 us).  2777 x 3001 x 1531, whose rows have no
+// 16-byte alignment: 24.2 us with scalar loads in two launches, 12.6 so.
+template <bool kPre, bool kReport, bool kLo>
+__global__ __launch_bounds__(256) void split_tiled_kernel(SplitArgs g) {
+  uint32_t b = blockIdx.x;
+  for (; b < g.a_blocks; b += gridDim.x) split_a_block<kPre, kReport, kLo>(g, b);
+  for (; b < g.blocks; b += gridDim.x) {
+    split_b_block<kPre, kReport, kLo>(g, b - g.a_blocks);
+    __syncthreads();  // this block's LDS words are read before the next block's are written
   }
 }
 
@@ -243,63 +294,54 @@ hipError_t launch_split_rows(int64_t rows, int64_t cols, const float* X, int64_t
   return hipGetLastError();
 }
 
-namespace {
-
-template <bool kPre, bool kReport>
-void enqueue_split_a(const Planes& p, int64_t M, int64_t K, const float* A, int64_t lda,
-                     float scale, const RangeOpts& opt, uint32_t stamp, hipStream_t stream) {
-  // Mp is a multiple of 256 and Kp of 64 (plan_planes).
-  const dim3 grid(static_cast<unsigned>((p.Kp + 127) / 128), grid_rows(p.Mp / 16));
-  const bool vec = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (lda % 4 == 0);
-  if (vec)
-    hipLaunchKernelGGL((split_a_tiled_kernel<true, kPre, kReport>), grid, dim3(256), 0, stream,
-                       M, K, A, lda, p.a_hi, p.a_lo, p.Mp, p.Kp, scale, p.row_max, opt.exp_a,
-                       p.range, stamp);
+hipError_t launch_split(const Planes& p, int64_t M, int64_t N, int64_t K, const float* A,
+                        int64_t lda, const float* B, int64_t ldb, float scale,
+                        const RangeOpts& opt, uint32_t a_stamp, uint32_t b_stamp, SplitPlanes what,
+                        hipStream_t stream) {
+  // Mp and Np are multiples of 256 and Kp of 64 (plan_planes).  Rows of the
+  // planes past M and N only feed entries of C that are never stored, so only
+  // kSplitPadded, for planes that outlive the call, fills them.
+  SplitArgs g{};
+  g.s = scale;
+  g.range = p.range;
+  g.Kp = p.Kp;
+  g.K = K;
+  const bool padded = what == kSplitPadded;
+  int64_t a_blocks = 0, b_blocks = 0;
+  if (B) {
+    // A block that sees |B_hi| s > 65504 writes range[kWordBOverflow] = stamp,
+    // every block range[kWordBStamp] = stamp, so the two words are equal
+    // afterwards exactly when this split found one; a fresh stamp per call
+    // makes a reset pass unnecessary.
+    g.B = B, g.ldb = ldb, g.N = N;
+    g.b_hi = p.b_hi, g.b_lo = p.b_lo;
+    g.col_max = p.col_max, g.exp_b = opt.exp_b, g.b_stamp = b_stamp;
+    b_blocks = p.Kp / (2 * kSlice) * ((padded ? p.Np : round_up(N, kPanel)) / kPanel);
+  }
+  if (A) {
+    g.A = A, g.lda = lda, g.M = M;
+    g.a_hi = p.a_hi, g.a_lo = p.a_lo;
+    g.row_max = p.row_max, g.exp_a = opt.exp_a, g.a_stamp = a_stamp;
+    a_blocks = (p.Kp + 127) / 128 * ((padded ? p.Mp : round_up(M, kABlockRows)) / kABlockRows);
+  }
+  // 2^32 blocks are at least 2^43 planes' bytes, more than any device holds.
+  const int64_t blocks = a_blocks + b_blocks;
+  if (blocks > UINT32_MAX) return hipErrorInvalidValue;
+  g.a_blocks = static_cast<uint32_t>(a_blocks);
+  g.blocks = static_cast<uint32_t>(blocks);
+  // At most 2^22 workgroups (a grid dimension holds less than 2^32 threads);
+  // past that each takes several blocks.
+  const dim3 grid(std::min(g.blocks, 1u << 22));
+  if (what == kSplitHigh)
+    hipLaunchKernelGGL((split_tiled_kernel<false, false, false>), grid, dim3(256), 0, stream, g);
+  else if (opt.prescale && opt.report)
+    hipLaunchKernelGGL((split_tiled_kernel<true, true, true>), grid, dim3(256), 0, stream, g);
+  else if (opt.prescale)
+    hipLaunchKernelGGL((split_tiled_kernel<true, false, true>), grid, dim3(256), 0, stream, g);
+  else if (opt.report)
+    hipLaunchKernelGGL((split_tiled_kernel<false, true, true>), grid, dim3(256), 0, stream, g);
   else
-    hipLaunchKernelGGL((split_a_tiled_kernel<false, kPre, kReport>), grid, dim3(256), 0, stream,
-                       M, K, A, lda, p.a_hi, p.a_lo, p.Mp, p.Kp, scale, p.row_max, opt.exp_a,
-                       p.range, stamp);
-}
-
-template <bool kPre, bool kReport>
-void enqueue_split_b(const Planes& p, int64_t K, int64_t N, const float* B, int64_t ldb,
-                     float scale, const RangeOpts& opt, uint32_t stamp, hipStream_t stream) {
-  // One workgroup per two tiles: Kp / 32 k blocks x Np / 128 panels (Np / 128
-  // <= 65535 is checked by the C-ABI).
-  const dim3 grid(static_cast<unsigned>(p.Kp / (2 * kSlice)), static_cast<unsigned>(p.Np / kPanel));
-  const bool vec = (reinterpret_cast<uintptr_t>(B) % 16 == 0) && (ldb % 4 == 0);
-  if (vec)
-    hipLaunchKernelGGL((split_b_tiled_kernel<true, kPre, kReport>), grid, dim3(256), 0, stream,
-                       K, N, B, ldb, p.b_hi, p.b_lo, p.Kp, scale, p.col_max, opt.exp_b, p.range,
-                       stamp);
-  else
-    hipLaunchKernelGGL((split_b_tiled_kernel<false, kPre, kReport>), grid, dim3(256), 0, stream,
-                       K, N, B, ldb, p.b_hi, p.b_lo, p.Kp, scale, p.col_max, opt.exp_b, p.range,
-                       stamp);
-}
-
-}  // namespace
-
-hipError_t launch_split_a(const Planes& p, int64_t M, int64_t K, const float* A, int64_t lda,
-                          float scale, const RangeOpts& opt, uint32_t stamp, hipStream_t stream) {
-  if (opt.prescale && opt.report) enqueue_split_a<true, true>(p, M, K, A, lda, scale, opt, stamp, stream);
-  else if (opt.prescale) enqueue_split_a<true, false>(p, M, K, A, lda, scale, opt, stamp, stream);
-  else if (opt.report) enqueue_split_a<false, true>(p, M, K, A, lda, scale, opt, stamp, stream);
-  else enqueue_split_a<false, false>(p, M, K, A, lda, scale, opt, stamp, stream);
-  return hipGetLastError();
-}
-
-hipError_t launch_split_b(const Planes& p, int64_t K, int64_t N, const float* B, int64_t ldb,
-                          float scale, const RangeOpts& opt, uint32_t stamp,
-                          hipStream_t stream) {
-  // Every workgroup writes range[kWordBStamp] = stamp and the ones that see
-  // an FP16 overflow of s B_hi write range[kWordBOverflow] = stamp, so the two
-  // words are equal afterwards exactly when this split found one; a fresh
-  // stamp per call makes a reset pass unnecessary.
-  if (opt.prescale && opt.report) enqueue_split_b<true, true>(p, K, N, B, ldb, scale, opt, stamp, stream);
-  else if (opt.prescale) enqueue_split_b<true, false>(p, K, N, B, ldb, scale, opt, stamp, stream);
-  else if (opt.report) enqueue_split_b<false, true>(p, K, N, B, ldb, scale, opt, stamp, stream);
-  else enqueue_split_b<false, false>(p, K, N, B, ldb, scale, opt, stamp, stream);
+    hipLaunchKernelGGL((split_tiled_kernel<false, false, true>), grid, dim3(256), 0, stream, g);
   return hipGetLastError();
 }
 
