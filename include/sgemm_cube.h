@@ -35,7 +35,9 @@
  *     Eq. split_error (Sec. 4.2); they are still computed as defined.
  *     sgemm_cube_ex adds power-of-two pre-scaling and a range report.
  *   - Thread-safe; the library keeps no per-call state, except that calls of
- *     sgemm_cube_noalloc that overlap on one GPU share its fixed workspace.
+ *     sgemm_cube_noalloc that overlap on one GPU share its fixed workspace, and
+ *     the null stream's calls of sgemm_cube and sgemm_cube_hgemm, in turn, a
+ *     kept one.
  */
 #ifndef SGEMM_CUBE_H_
 #define SGEMM_CUBE_H_
@@ -91,7 +93,9 @@ typedef enum {
  * Needs device workspace of sgemm_cube_workspace_size(M, N, K, accum_order)
  * bytes, which this entry point takes stream-ordered from a library-owned
  * memory pool (hipMallocFromPoolAsync / hipFreeAsync on `stream`); failure ->
- * SGEMM_CUBE_ERR_ALLOC.  Use sgemm_cube_ws to pass your own workspace.
+ * SGEMM_CUBE_ERR_ALLOC.  On the null stream a workspace of up to 1 GiB per GPU
+ * is kept for the next call instead of freed (and given up when the pool
+ * cannot supply another call).  Use sgemm_cube_ws to pass your own workspace.
  */
 int sgemm_cube(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                int64_t ldb, float* C, int64_t ldc, float scale, int accum_order,

@@ -247,7 +247,7 @@ std::mutex g_pool_mu;
 constexpr int kMaxDevices = 64;
 hipMemPool_t g_pools[kMaxDevices] = {};
 
-int get_pool(hipMemPool_t* out) {
+int get_pool(hipMemPool_t* out, int* device) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
     return SGEMM_CUBE_ERR_HIP;
@@ -268,7 +268,44 @@ int get_pool(hipMemPool_t* out) {
     g_pools[dev] = pool;
   }
   *out = g_pools[dev];
+  *device = dev;
   return SGEMM_CUBE_OK;
+}
+
+// The workspace that a device's null stream keeps from call to call, taken from
+// the pool.  hipFreeAsync blocks the host until the stream reaches it (10 us at
+// the smallest call, 0.8 of the GEMM's time at the largest), so a call that
+// frees its workspace cannot be queued behind another.  The null stream is one
+// queue for the life of the process, so there the next call's kernels are
+// ordered after this call's and may reuse its workspace; other streams' handles
+// can name another queue after a destroy (or per thread), so they keep the
+// stream-ordered allocation.  A host thread holds `mu` while it enqueues one
+// call: the kernels of two calls must not interleave on the stream.  At most
+// kNullWorkspaceMax bytes per device are kept (a larger call allocates its
+// own), and they go back to the pool when an allocation fails.
+struct NullWorkspace {
+  std::mutex mu;
+  void* ptr = nullptr;
+  size_t bytes = 0;
+};
+NullWorkspace g_null_ws[kMaxDevices];
+constexpr size_t kNullWorkspaceMax = size_t{1} << 30;
+
+// Stream-ordered allocation from the pool; on failure clears the runtime's last
+// error, so that it is not reported by the launch check of a later call on this
+// thread.
+bool pool_alloc(void** ws, size_t need, hipMemPool_t pool, hipStream_t stream) {
+  *ws = nullptr;
+  if (hipMallocFromPoolAsync(ws, need, pool, stream) == hipSuccess && *ws) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+// Gives the kept workspace back to the pool; the caller holds w.mu.
+void release(NullWorkspace& w) {
+  if (w.ptr) (void)hipFreeAsync(w.ptr, nullptr);
+  w.ptr = nullptr;
+  w.bytes = 0;
 }
 
 int run_allocating(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
@@ -277,17 +314,32 @@ int run_allocating(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
   const size_t need = ws_size(M, N, K);
   if (need == 0) return run(M, N, K, A, lda, B, ldb, C, ldc, scale, variant, nullptr, stream);
   hipMemPool_t pool = nullptr;
-  int st = get_pool(&pool);
+  int dev = 0;
+  int st = get_pool(&pool, &dev);
   if (st != SGEMM_CUBE_OK) {
     (void)hipGetLastError();
     return st;
   }
+  NullWorkspace& kept = g_null_ws[dev];
+  if (stream == nullptr && need <= kNullWorkspaceMax) {
+    std::unique_lock<std::mutex> lock(kept.mu, std::try_to_lock);
+    if (lock.owns_lock()) {  // else another thread is enqueueing: allocate below
+      if (kept.bytes < need) {
+        release(kept);
+        if (!pool_alloc(&kept.ptr, need, pool, stream)) return SGEMM_CUBE_ERR_ALLOC;
+        kept.bytes = need;
+      }
+      return run(M, N, K, A, lda, B, ldb, C, ldc, scale, variant, kept.ptr, stream);
+    }
+  }
   void* ws = nullptr;
-  if (hipMallocFromPoolAsync(&ws, need, pool, stream) != hipSuccess || !ws) {
-    // Clear the runtime's last error, so that it is not reported by the
-    // launch check of a later call on this thread.
-    (void)hipGetLastError();
-    return SGEMM_CUBE_ERR_ALLOC;
+  if (!pool_alloc(&ws, need, pool, stream)) {
+    {
+      std::lock_guard<std::mutex> lock(kept.mu);
+      if (!kept.ptr) return SGEMM_CUBE_ERR_ALLOC;
+      release(kept);
+    }
+    if (!pool_alloc(&ws, need, pool, stream)) return SGEMM_CUBE_ERR_ALLOC;
   }
   st = run(M, N, K, A, lda, B, ldb, C, ldc, scale, variant, ws, stream);
   if (hipFreeAsync(ws, stream) != hipSuccess && st == SGEMM_CUBE_OK) st = SGEMM_CUBE_ERR_HIP;
