@@ -230,7 +230,12 @@ int run(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const floa
   if (launch_split(p, M, N, K, A, lda, B, ldb, scale, opt, a_stamp, b_stamp,
                    variant == kHiOnly ? kSplitHigh : kSplitRows, stream) != hipSuccess)
     return SGEMM_CUBE_ERR_HIP;
-  if (launch_gemm(p, M, N, C, ldc, scale, variant, stream) != hipSuccess)
+  if (const int tile = small_gemm_tile(M, N, variant))
+    return launch_gemm_small(tile, p, M, N, C, ldc, scale, variant, stream, opt, report) ==
+                   hipSuccess
+               ? SGEMM_CUBE_OK
+               : SGEMM_CUBE_ERR_HIP;
+  if (launch_gemm_wide(p, M, N, C, ldc, scale, variant, stream) != hipSuccess)
     return SGEMM_CUBE_ERR_HIP;
   if (opt.prescale && launch_unscale(p, M, N, C, ldc, opt, stream) != hipSuccess)
     return SGEMM_CUBE_ERR_HIP;

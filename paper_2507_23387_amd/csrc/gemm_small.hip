@@ -72,6 +72,11 @@ struct SmallArgs {
   int64_t ldc;
   int M, N;
   float s, inv_s;
+  // Pre-scaling (row_max not null): C_ij is stored times 2^-(p_i + q_j).
+  const uint32_t* row_max;
+  const uint32_t* col_max;
+  int exp_a, exp_b;
+  uint32_t* report;  // range report word, or null
 };
 
 template <class S, int kFold>
@@ -277,7 +282,7 @@ __device__ __forceinline__ void small_tile(const SmallArgs& g, uint16_t* lds) {
   const int col0 = tn * S::kBN + wn * S::kWCols + (lane & 15);
   const int row0 = tm * S::kBM + wm * S::kWRows + (lane >> 4) * 4;
   const bool full = (tm + 1) * S::kBM <= g.M && (tn + 1) * S::kBN <= g.N;
-  store_tile16<kRT, kCT>(g.C, g.ldc, g.M, g.N, row0, col0, full, [&](int i, int j, int r) {
+  auto value = [&](int i, int j, int r) {
     if constexpr (kTerm)
       return __builtin_fmaf(xb[kTerm ? i : 0][kTerm ? j : 0][r], g.inv_s,
                             __builtin_fmaf(xa[kTerm ? i : 0][kTerm ? j : 0][r], g.inv_s,
@@ -286,7 +291,30 @@ __device__ __forceinline__ void small_tile(const SmallArgs& g, uint16_t* lds) {
       return acc[i][j][r] * g.inv_s;
     else
       return acc[i][j][r];
-  });
+  };
+  if constexpr (kFold != kHiFold) {
+    if (g.report && blockIdx.x == 0 && threadIdx.x == 0) *g.report = range_report_bits(g.range);
+    if (g.row_max) {
+      int p[kRT][4], q[kCT];
+#pragma unroll
+      for (int i = 0; i < kRT; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = row0 + 16 * i + r;
+          p[i][r] = row < g.M ? prescale_shift(g.row_max[row], g.exp_a) : 0;
+        }
+#pragma unroll
+      for (int j = 0; j < kCT; ++j) {
+        const int col = col0 + 16 * j;
+        q[j] = col < g.N ? prescale_shift(g.col_max[col], g.exp_b) : 0;
+      }
+      store_tile16<kRT, kCT>(g.C, g.ldc, g.M, g.N, row0, col0, full, [&](int i, int j, int r) {
+        return __builtin_ldexpf(value(i, j, r), -(p[i][r] + q[j]));
+      });
+      return;
+    }
+  }
+  store_tile16<kRT, kCT>(g.C, g.ldc, g.M, g.N, row0, col0, full, value);
 }
 
 template <int V, int kBM, int kBN, int kWM, int kWN, int kStages>
@@ -310,7 +338,7 @@ __global__ __launch_bounds__(64 * kWM * kWN, 1) void gemm_small_kernel(SmallArgs
 
 template <int V, int kBM, int kBN, int kWM, int kWN, int kStages>
 hipError_t launch_small(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc, float s,
-                        hipStream_t stream) {
+                        hipStream_t stream, const RangeOpts& opt, uint32_t* report) {
   using S = SmallShape<kBM, kBN, kWM, kWN, kStages, V == kHiOnly>;
   static std::atomic<bool> done[kMaxDevices];
   const hipError_t attr =
@@ -318,7 +346,9 @@ hipError_t launch_small(const Planes& p, int64_t M, int64_t N, float* C, int64_t
   if (attr != hipSuccess) return attr;
   SmallArgs g{p.a_hi, p.a_lo, p.b_hi, p.b_lo, p.range, static_cast<int>(p.Kp),
               static_cast<int>((M + kBM - 1) / kBM), static_cast<int>((N + kBN - 1) / kBN),
-              C, ldc, static_cast<int>(M), static_cast<int>(N), s, 1.0f / s};
+              C, ldc, static_cast<int>(M), static_cast<int>(N), s, 1.0f / s,
+              opt.prescale ? p.row_max : nullptr, opt.prescale ? p.col_max : nullptr,
+              opt.exp_a, opt.exp_b, report};
   hipLaunchKernelGGL((gemm_small_kernel<V, kBM, kBN, kWM, kWN, kStages>),
                      dim3(g.tiles_m * g.tiles_n), dim3(S::kThreads), S::kLdsBytes, stream, g,
                      scaled_kernel_ok(s) ? 0 : 1);
@@ -327,16 +357,16 @@ hipError_t launch_small(const Planes& p, int64_t M, int64_t N, float* C, int64_t
 
 template <int V>
 hipError_t launch_config(int tile, const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,
-                         float s, hipStream_t stream) {
+                         float s, hipStream_t stream, const RangeOpts& opt, uint32_t* report) {
   switch (tile) {
-    case 32: return launch_small<V, 32, 32, 2, 2, 8>(p, M, N, C, ldc, s, stream);
+    case 32: return launch_small<V, 32, 32, 2, 2, 8>(p, M, N, C, ldc, s, stream, opt, report);
     case 64:
       if constexpr (V == kHiOnly)
-        return launch_small<V, 64, 64, 2, 2, 8>(p, M, N, C, ldc, s, stream);
+        return launch_small<V, 64, 64, 2, 2, 8>(p, M, N, C, ldc, s, stream, opt, report);
       else
-        return launch_small<V, 64, 64, 4, 2, 4>(p, M, N, C, ldc, s, stream);
+        return launch_small<V, 64, 64, 4, 2, 4>(p, M, N, C, ldc, s, stream, opt, report);
     case 128:
-      return launch_small<V, 128, 128, 2, 4, 4>(p, M, N, C, ldc, s, stream);
+      return launch_small<V, 128, 128, 2, 4, 4>(p, M, N, C, ldc, s, stream, opt, report);
     default: return hipErrorInvalidValue;
   }
 }
@@ -382,12 +412,17 @@ int small_gemm_tile(int64_t M, int64_t N, int variant) {
 }
 
 hipError_t launch_gemm_small(int tile, const Planes& p, int64_t M, int64_t N, float* C,
-                             int64_t ldc, float scale, int variant, hipStream_t stream) {
+                             int64_t ldc, float scale, int variant, hipStream_t stream,
+                             const RangeOpts& opt, uint32_t* report) {
   switch (variant) {
-    case kElementwise: return launch_config<kElementwise>(tile, p, M, N, C, ldc, scale, stream);
-    case kTermwise: return launch_config<kTermwise>(tile, p, M, N, C, ldc, scale, stream);
-    case kCrossFirst: return launch_config<kCrossFirst>(tile, p, M, N, C, ldc, scale, stream);
-    case kHiOnly: return launch_config<kHiOnly>(tile, p, M, N, C, ldc, scale, stream);
+    case kElementwise:
+      return launch_config<kElementwise>(tile, p, M, N, C, ldc, scale, stream, opt, report);
+    case kTermwise:
+      return launch_config<kTermwise>(tile, p, M, N, C, ldc, scale, stream, opt, report);
+    case kCrossFirst:
+      return launch_config<kCrossFirst>(tile, p, M, N, C, ldc, scale, stream, opt, report);
+    case kHiOnly:
+      return launch_config<kHiOnly>(tile, p, M, N, C, ldc, scale, stream, opt, report);
     default: return hipErrorInvalidValue;
   }
 }

@@ -114,6 +114,16 @@ constexpr int kWordAClass = 3;
 constexpr int kWordBClass = 7;
 constexpr int kRangeClasses = 4;
 
+// OR of the range classes stamped by the last split of each operand.
+__device__ inline uint32_t range_report_bits(const uint32_t* range) {
+  uint32_t bits = 0;
+  for (int b = 0; b < kRangeClasses; ++b) {
+    if (range[kWordAClass + b] == range[kWordAStamp]) bits |= 1u << b;
+    if (range[kWordBClass + b] == range[kWordBStamp]) bits |= 1u << b;
+  }
+  return bits;
+}
+
 // Options of one call: power-of-two pre-scaling of rows of A and columns of B
 // (target exponents of their largest magnitudes), and the range report.
 struct RangeOpts {
@@ -171,9 +181,12 @@ hipError_t launch_range_report(const Planes& p, bool empty, uint32_t* out, hipSt
 int small_gemm_tile(int64_t M, int64_t N, int variant);
 
 // The GEMM on tile x tile tiles (gemm_small.hip).  Same results as the 256-wide
-// kernels, bit for bit, range fallbacks included.
+// kernels, bit for bit, range fallbacks included.  With opt.prescale it also
+// applies launch_unscale's powers of two to C as it stores it, and with
+// `report` not null it writes launch_range_report's word.
 hipError_t launch_gemm_small(int tile, const Planes& p, int64_t M, int64_t N, float* C,
-                             int64_t ldc, float scale, int variant, hipStream_t stream);
+                             int64_t ldc, float scale, int variant, hipStream_t stream,
+                             const RangeOpts& opt = RangeOpts{}, uint32_t* report = nullptr);
 
 // The 256-wide kernels (gemm.hip) on prepared planes.
 hipError_t launch_gemm_wide(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,

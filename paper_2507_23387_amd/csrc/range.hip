@@ -12,54 +12,128 @@
 namespace sgc {
 namespace {
 
-// Largest finite |A[i, :]| per row, one workgroup per row; as a side job the
-// grid also clears the column maxima that absmax_cols_kernel raises next.
+// Four consecutive floats at any 4-byte aligned address (one 16-byte load).
+typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+// max(m, |a|), skipping inf and NaN.
+__device__ __forceinline__ float max_finite(float m, float a) {
+  const float b = __builtin_fabsf(a);
+  return b <= 3.4028235e38f ? __builtin_fmaxf(m, b) : m;
+}
+
+constexpr int kAbsRows = 4;     // rows of A per workgroup, one per wave
+constexpr int kAbsCols = 32;    // columns of B per workgroup: one 128-byte line per row of B
+constexpr int kAbsUnroll = 8;   // loads in flight per thread
+
+// Largest finite |A[i, :]| of the workgroup's four rows, a wave per row.
+__device__ __forceinline__ void absmax_rows(int64_t block, int64_t M, int64_t K,
+                                            const float* __restrict__ A, int64_t lda,
+                                            uint32_t* __restrict__ row_max) {
+  const int lane = threadIdx.x & 63;
+  const int64_t i = block * kAbsRows + (threadIdx.x >> 6);
+  if (i >= M) return;
+  const float* const row = A + i * lda;
+  float m = 0.0f;
+  int64_t k = lane * 4;
+  for (; k + 3 + (kAbsUnroll - 1) * 256 < K; k += kAbsUnroll * 256) {
+    floatx4_u v[kAbsUnroll];
+#pragma unroll
+    for (int u = 0; u < kAbsUnroll; ++u)
+      v[u] = *reinterpret_cast<const floatx4_u*>(row + k + u * 256);
+#pragma unroll
+    for (int u = 0; u < kAbsUnroll; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m = max_finite(m, v[u][e]);
+  }
+  for (; k < K; k += 256)
+    for (int e = 0; e < 4 && k + e < K; ++e) m = max_finite(m, row[k + e]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off));
+  if (lane == 0) row_max[i] = __builtin_bit_cast(uint32_t, m);
+}
+
+// Largest finite |B[k0 .. k1-1, j]| of 32 columns: thread t takes columns
+// 4 (t % 8) .. + 3 of every 32nd row, then the workgroup reduces in LDS.
+// kAtomic: raise the maxima (several workgroups per column; non-negative floats
+// order like their bit patterns), else store them.
+template <bool kAtomic>
+__device__ __forceinline__ void absmax_cols(int64_t strip, int64_t k0, int64_t k1, int64_t N,
+                                            const float* __restrict__ B, int64_t ldb,
+                                            uint32_t* __restrict__ col_max) {
+  __shared__ float part[32][kAbsCols + 1];
+  const int t = threadIdx.x;
+  const int64_t j = strip * kAbsCols + (t & 7) * 4;
+  float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  int64_t k = k0 + (t >> 3);
+  if (j + 3 < N) {
+    for (; k + (kAbsUnroll - 1) * 32 < k1; k += kAbsUnroll * 32) {
+      floatx4_u v[kAbsUnroll];
+#pragma unroll
+      for (int u = 0; u < kAbsUnroll; ++u)
+        v[u] = *reinterpret_cast<const floatx4_u*>(B + (k + u * 32) * ldb + j);
+#pragma unroll
+      for (int u = 0; u < kAbsUnroll; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m[e] = max_finite(m[e], v[u][e]);
+    }
+  }
+  for (; k < k1; k += 32)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (j + e < N) m[e] = max_finite(m[e], B[k * ldb + j + e]);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[t >> 3][(t & 7) * 4 + e] = m[e];
+  __syncthreads();
+  if (t < kAbsCols && strip * kAbsCols + t < N) {
+    float r = part[0][t];
+#pragma unroll
+    for (int i = 1; i < 32; ++i) r = __builtin_fmaxf(r, part[i][t]);
+    uint32_t* const out = col_max + strip * kAbsCols + t;
+    if constexpr (kAtomic) {
+      if (r > 0.0f) atomicMax(out, __builtin_bit_cast(uint32_t, r));
+    } else {
+      *out = __builtin_bit_cast(uint32_t, r);
+    }
+  }
+}
+
+// Row maxima of A (the first row_blocks workgroups) and column maxima of B.  A
+// column's workgroup walks all of K: 1024^3 6 us in this one launch, against 4 +
+// 18.5 us of the two kernels below's predecessors.
+__global__ __launch_bounds__(256) void absmax_kernel(uint32_t row_blocks, int64_t M, int64_t N,
+                                                     int64_t K, const float* __restrict__ A,
+                                                     int64_t lda, const float* __restrict__ B,
+                                                     int64_t ldb, uint32_t* __restrict__ row_max,
+                                                     uint32_t* __restrict__ col_max) {
+  if (blockIdx.x < row_blocks)
+    absmax_rows(blockIdx.x, M, K, A, lda, row_max);
+  else
+    absmax_cols<false>(blockIdx.x - row_blocks, 0, K, N, B, ldb, col_max);
+}
+
+// Row maxima of A; as a side job the grid clears the column maxima that
+// absmax_cols_kernel raises next.
 __global__ __launch_bounds__(256) void absmax_rows_kernel(int64_t M, int64_t K,
                                                           const float* __restrict__ A,
                                                           int64_t lda,
                                                           uint32_t* __restrict__ row_max,
                                                           uint32_t* __restrict__ col_max,
-                                                          int64_t Np) {
-  __shared__ float part[4];
-  const int t = threadIdx.x;
-  for (int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + t; j < Np;
+                                                          int64_t N) {
+  for (int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; j < N;
        j += static_cast<int64_t>(gridDim.x) * 256)
     col_max[j] = 0u;
-  for (int64_t i = blockIdx.x; i < M; i += gridDim.x) {
-    float m = 0.0f;
-    for (int64_t k = t; k < K; k += 256) {
-      const float a = __builtin_fabsf(A[i * lda + k]);
-      if (a <= 3.4028235e38f) m = __builtin_fmaxf(m, a);  // skips inf and NaN
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off));
-    if ((t & 63) == 0) part[t >> 6] = m;
-    __syncthreads();
-    if (t == 0)
-      row_max[i] = __builtin_bit_cast(
-          uint32_t, __builtin_fmaxf(__builtin_fmaxf(part[0], part[1]),
-                                    __builtin_fmaxf(part[2], part[3])));
-    __syncthreads();
-  }
+  for (int64_t b = blockIdx.x; b * kAbsRows < M; b += gridDim.x)
+    absmax_rows(b, M, K, A, lda, row_max);
 }
 
-// Largest finite |B[:, j]| per column: workgroup (column block, row block)
-// reduces 64 rows of 256 columns and raises the column maxima atomically
-// (non-negative floats order like their bit patterns).
+// Column maxima of B, kAbsChunk rows of B per workgroup.
+constexpr int64_t kAbsChunk = 1024;
 __global__ __launch_bounds__(256) void absmax_cols_kernel(int64_t K, int64_t N,
                                                           const float* __restrict__ B,
                                                           int64_t ldb,
                                                           uint32_t* __restrict__ col_max) {
-  const int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (j >= N) return;
-  const int64_t k0 = static_cast<int64_t>(blockIdx.y) * 64;
-  const int64_t k1 = k0 + 64 < K ? k0 + 64 : K;
-  float m = 0.0f;
-  for (int64_t k = k0; k < k1; ++k) {
-    const float b = __builtin_fabsf(B[k * ldb + j]);
-    if (b <= 3.4028235e38f) m = __builtin_fmaxf(m, b);
-  }
-  if (m > 0.0f) atomicMax(col_max + j, __builtin_bit_cast(uint32_t, m));
+  const int64_t k0 = blockIdx.y * kAbsChunk;
+  absmax_cols<true>(blockIdx.x, k0, k0 + kAbsChunk < K ? k0 + kAbsChunk : K, N, B, ldb, col_max);
 }
 
 // C_ij := 2^-(p_i + q_j) C_ij, one rounding (ldexp).
@@ -80,14 +154,7 @@ __global__ __launch_bounds__(256) void unscale_kernel(int64_t M, int64_t N, floa
 // *out = OR of the range classes stamped by the last split of each operand.
 __global__ void range_report_kernel(const uint32_t* __restrict__ range, int empty,
                                     uint32_t* __restrict__ out) {
-  uint32_t bits = 0;
-  if (!empty) {
-    for (int b = 0; b < kRangeClasses; ++b) {
-      if (range[kWordAClass + b] == range[kWordAStamp]) bits |= 1u << b;
-      if (range[kWordBClass + b] == range[kWordBStamp]) bits |= 1u << b;
-    }
-  }
-  *out = bits;
+  *out = empty ? 0u : range_report_bits(range);
 }
 
 inline unsigned grid_y(int64_t rows) {
@@ -98,12 +165,24 @@ inline unsigned grid_y(int64_t rows) {
 
 hipError_t launch_absmax(const Planes& p, int64_t M, int64_t N, int64_t K, const float* A,
                          int64_t lda, const float* B, int64_t ldb, hipStream_t stream) {
-  const int64_t rows_grid = M < (int64_t{1} << 30) ? (M > 0 ? M : 1) : (int64_t{1} << 30);
+  const int64_t row_blocks = (M + kAbsRows - 1) / kAbsRows;
+  const int64_t strips = (N + kAbsCols - 1) / kAbsCols;
+  // One launch while a column's workgroup walks at most 4096 rows (about 15
+  // us) and the blocks fit a grid; past that the columns are cut along K, into
+  // maxima that a launch before clears.
+  if (K <= 4096 && row_blocks + strips <= (1 << 23)) {
+    hipLaunchKernelGGL(absmax_kernel, dim3(static_cast<unsigned>(row_blocks + strips)), dim3(256),
+                       0, stream, static_cast<uint32_t>(row_blocks), M, N, K, A, lda, B, ldb,
+                       p.row_max, p.col_max);
+    return hipGetLastError();
+  }
+  const int64_t rows_grid = row_blocks < (1 << 23) ? row_blocks : (1 << 23);
   hipLaunchKernelGGL(absmax_rows_kernel, dim3(static_cast<unsigned>(rows_grid)), dim3(256), 0,
-                     stream, M, K, A, lda, p.row_max, p.col_max, p.Np);
+                     stream, M, K, A, lda, p.row_max, p.col_max, N);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const dim3 grid(static_cast<unsigned>((N + 255) / 256), static_cast<unsigned>((K + 63) / 64));
+  const dim3 grid(static_cast<unsigned>(strips),
+                  static_cast<unsigned>((K + kAbsChunk - 1) / kAbsChunk));
   hipLaunchKernelGGL(absmax_cols_kernel, grid, dim3(256), 0, stream, K, N, B, ldb, p.col_max);
   return hipGetLastError();
 }

@@ -82,3 +82,33 @@ def test_cross_first_and_baseline_against_the_oracle(gpu, shape, kind):
     order = "hi_only" if kind == "hgemm" else "elementwise_cross_first"
     want = oracle.sgemm_rows(A, B, rows, 2048.0, order, kb=32)
     assert_parity(C[rows], want, K, abs_ab(A, B, rows), f"small tiles {kind} {shape}")
+
+
+@pytest.mark.parametrize("order", ["elementwise", "termwise"])
+@pytest.mark.parametrize("shape", [(5, 33, 4096), (35, 31, 4097), (70, 300, 9000), (1100, 1030, 80)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_prescaled_with_the_report(gpu, shape, order):
+    """Pre-scaling and the report around the small tiles: the maxima in one
+    launch (K <= 4096) and cut along K, the powers of two taken back out in
+    the GEMM's store, on rows and columns from 2^-28 to 2^24 and rows of no
+    alignment, against the oracle's pre-scaled product."""
+    import torch
+
+    from paper_2507_23387_amd import binding
+    from tests.gpu_util import padded
+
+    M, N, K = shape
+    rng = np.random.default_rng(M + K)
+    A = (rng.uniform(-1, 1, (M, K)) * np.ldexp(1.0, rng.integers(-28, 25, (M, 1)))).astype(np.float32)
+    B = (rng.uniform(-1, 1, (K, N)) * np.ldexp(1.0, rng.integers(-28, 25, (1, N)))).astype(np.float32)
+    A[M - 1, K - 1] = np.float32(2.0**30)  # the last entry of a row holds its maximum
+    log(f"prescale {order} {M}x{N}x{K}")
+    _, vA = padded(A, K + 1, offset=1)
+    _, vB = padded(B, N + 3, offset=2)
+    C, bits = binding.matmul_ex(vA[:, :K], vB[:, :N], order=order, prescale=True, report=True)
+    torch.cuda.synchronize()
+    rows = band_rows(M, K, band=64)
+    want = oracle.sgemm_prescaled(A[rows], B, 2048.0, order, kb=32)
+    assert_parity(C.cpu().numpy()[rows], want, K, abs_ab(A, B, rows), f"prescale {shape}")
+    # Entries far below their row's largest have subnormal high words, no other class occurs.
+    assert int(bits.item()) & ~binding.RANGE_HI_SUBNORMAL == 0
