@@ -13,15 +13,17 @@
 //
 // What bounds it: at these sizes a 256 x 256 kernel runs on M N / 65536 compute
 // units at 1.6 us per 32-wide k-step.  A smaller tile spreads the same k-steps
-// over more compute units but copies and reads more LDS bytes per MFMA: a
-// 64 x 64 step reads 48 KiB (8 waves of 16 x 32) and copies 16 KiB through LDS
-// for 96 cycles of MFMAs per SIMD and takes 0.24 us, near the 128 B per clock
-// of the LDS; a 32 x 32 step takes 0.11 us, the latency of a barrier, an LDS
-// read and three dependent MFMAs.  So the tile is the smallest that still
-// leaves few workgroups per compute unit.  GEMM alone, elementwise, wide kernel
-// against this one: 256^3 25.9 and 4.2 us, 300 x 200 x 1024 60 and 6.5,
-// 1024^3 60 and 12.2, 48 x 4096 x 4096 196 and 18, 2048 x 2048 x 2816 142 and
-// 65; hgemm at 2048 x 2048 x 2816 91 and 31 us.
+// over more compute units but moves more LDS bytes per MFMA.  A 64 x 64 step is
+// 192 cycles of MFMAs per SIMD, 256 cycles of LDS reads and 128 of the copies'
+// LDS writes at 128 B per clock, and a barrier, and takes about 500 cycles (0.23
+// us; without the copies 25 of 31 us at 1024 x 1024 x 4096 termwise, without the
+// reads 28, without both 19).  A 32 x 32 step takes 0.1 us, most of it the
+// barrier and an LDS read's latency.  So the tile is the smallest that still
+// leaves few workgroups per compute unit.  GEMM alone, wide kernel against this
+// one: elementwise 256^3 25.8 and 4.0 us, 300 x 200 x 1024 61 and 6.2, 1024^3
+// 60 and 11.2, 48 x 4096 x 4096 196 and 17.4, 2048 x 2048 x 2816 141 and 59;
+// termwise 34.4 and 10.3 at 1024^3; the FP16 baseline 70 and 27 at 2048 x 2048
+// x 2816.
 #include <algorithm>
 #include <atomic>
 
@@ -137,20 +139,18 @@ __device__ __forceinline__ void small_tile(const SmallArgs& g, uint16_t* lds) {
     return *reinterpret_cast<const half8*>(lds + slot * S::kSlot + p * S::kBPlane + b_off[j & 1] +
                                            j * 16 * kSlice);
   };
+  constexpr bool kScaled = kFold == kElScaled || kFold == kCrScaled;
   struct Frags {
     half8 ah[kRT], al[kRT], bh[kCT], bl[kCT];
+    half8 bs[kScaled ? kCT : 1];  // s B_hi, exact (gemm.hip)
   };
-  auto read = [&](Frags& f, int slot) {
-#pragma unroll
-    for (int i = 0; i < kRT; ++i) {
-      f.ah[i] = rd_a(slot, 0, i);
-      if constexpr (kFold != kHiFold) f.al[i] = rd_a(slot, 1, i);
-    }
-#pragma unroll
-    for (int j = 0; j < kCT; ++j) {
-      f.bh[j] = rd_b(slot, 0, j);
-      if constexpr (kFold != kHiFold) f.bl[j] = rd_b(slot, 1, j);
-    }
+  // Read r of a step's fragments: B_hi, A_hi, A_lo, B_lo, the order of first use.
+  auto read_one = [&](Frags& f, int slot, auto Rc) {
+    constexpr int r = decltype(Rc)::value;
+    if constexpr (r < kCT) f.bh[r] = rd_b(slot, 0, r);
+    else if constexpr (r < kCT + kRT) f.ah[r - kCT] = rd_a(slot, 0, r - kCT);
+    else if constexpr (r < kCT + 2 * kRT) f.al[r - kCT - kRT] = rd_a(slot, 1, r - kCT - kRT);
+    else f.bl[r - kCT - 2 * kRT] = rd_b(slot, 1, r - kCT - 2 * kRT);
   };
 
   const _Float16 s16 = static_cast<_Float16>(g.s);
@@ -164,64 +164,47 @@ __device__ __forceinline__ void small_tile(const SmallArgs& g, uint16_t* lds) {
       acc[i][j] = floatx4{};
       if constexpr (kTerm) xa[i][j] = xb[i][j] = floatx4{};
     }
-  // The MFMAs of one step; `between(n)` runs after group n of them.
-  auto multiply = [&](const Frags& f, auto between) {
+  // The MFMAs of one step, in the order of gemm.hip's kernels per accumulator;
+  // `after(m)` runs after the m-th of them.
+  constexpr int kTile = kRT * kCT;
+  constexpr int kMfmas = kFold == kHiFold ? kTile : 3 * kTile;
+  auto multiply = [&](const Frags& f, auto after) {
     if constexpr (kFold == kElScaled || kFold == kTermFold || kFold == kHiFold) {
-      half8 bs[kCT];
-#pragma unroll
-      for (int j = 0; j < kCT; ++j) bs[j] = kFold == kElScaled ? f.bh[j] * s8 : f.bh[j];
-      static_for<kCT>([&](auto J) {
-        constexpr int j = decltype(J)::value;
-#pragma unroll
-        for (int i = 0; i < kRT; ++i) acc[i][j] = mfma16(f.ah[i], bs[j], acc[i][j]);
-        between(std::integral_constant<int, j>{});
+      static_for<kMfmas>([&](auto Mc) {
+        constexpr int m = decltype(Mc)::value, g = m / kTile, j = m % kTile / kRT, i = m % kRT;
+        if constexpr (g == 0) {
+          acc[i][j] = mfma16(f.ah[i], kFold == kElScaled ? f.bs[kScaled ? j : 0] : f.bh[j], acc[i][j]);
+        } else if constexpr (g == 1) {
+          floatx4& x = kTerm ? xa[kTerm ? i : 0][kTerm ? j : 0] : acc[i][j];
+          x = mfma16(f.al[i], f.bh[j], x);
+        } else {
+          floatx4& x = kTerm ? xb[kTerm ? i : 0][kTerm ? j : 0] : acc[i][j];
+          x = mfma16(f.ah[i], f.bl[j], x);
+        }
+        after(Mc);
       });
-      if constexpr (kFold != kHiFold) {
-        static_for<kCT>([&](auto J) {
-          constexpr int j = decltype(J)::value;
-#pragma unroll
-          for (int i = 0; i < kRT; ++i) {
-            floatx4& x = kTerm ? xa[kTerm ? i : 0][kTerm ? j : 0] : acc[i][j];
-            x = mfma16(f.al[i], f.bh[j], x);
-          }
-          between(std::integral_constant<int, kCT + j>{});
-        });
-        static_for<kCT>([&](auto J) {
-          constexpr int j = decltype(J)::value;
-#pragma unroll
-          for (int i = 0; i < kRT; ++i) {
-            floatx4& x = kTerm ? xb[kTerm ? i : 0][kTerm ? j : 0] : acc[i][j];
-            x = mfma16(f.ah[i], f.bl[j], x);
-          }
-          between(std::integral_constant<int, 2 * kCT + j>{});
-        });
-      }
     } else {
       const floatx4 zero{};
       static_for<kCT>([&](auto J) {
         constexpr int j = decltype(J)::value;
         floatx4 t1[kRT], t2[kRT];
-        half8 bs{};
-        if constexpr (kFold == kCrScaled) bs = f.bh[j] * s8;
-#pragma unroll
-        for (int i = 0; i < kRT; ++i) {
-          if constexpr (kFold == kElUnscaled) acc[i][j] = mfma16(f.ah[i], f.bh[j], acc[i][j]);
-          if constexpr (kFold == kCrUnscaled) t2[i] = mfma16(f.ah[i], f.bh[j], zero);
-        }
-#pragma unroll
-        for (int i = 0; i < kRT; ++i) t1[i] = mfma16(f.al[i], f.bh[j], zero);
-        between(std::integral_constant<int, 3 * j>{});
-#pragma unroll
-        for (int i = 0; i < kRT; ++i) {
-          if constexpr (kFold == kElUnscaled) t2[i] = mfma16(f.ah[i], f.bl[j], zero);
-          else t1[i] = mfma16(f.ah[i], f.bl[j], t1[i]);
-        }
-        between(std::integral_constant<int, 3 * j + 1>{});
-        if constexpr (kFold == kCrScaled) {
-#pragma unroll
-          for (int i = 0; i < kRT; ++i) t1[i] = mfma16(f.ah[i], bs, t1[i]);
-        }
-        between(std::integral_constant<int, 3 * j + 2>{});
+        static_for<3 * kRT>([&](auto Mc) {
+          constexpr int m = decltype(Mc)::value, g = m / kRT, i = m % kRT;
+          if constexpr (kFold == kElUnscaled) {
+            if constexpr (g == 0) acc[i][j] = mfma16(f.ah[i], f.bh[j], acc[i][j]);
+            else if constexpr (g == 1) t1[i] = mfma16(f.al[i], f.bh[j], zero);
+            else t2[i] = mfma16(f.ah[i], f.bl[j], zero);
+          } else if constexpr (kFold == kCrScaled) {
+            if constexpr (g == 0) t1[i] = mfma16(f.al[i], f.bh[j], zero);
+            else if constexpr (g == 1) t1[i] = mfma16(f.ah[i], f.bl[j], t1[i]);
+            else t1[i] = mfma16(f.ah[i], f.bs[kScaled ? j : 0], t1[i]);
+          } else {
+            if constexpr (g == 0) t2[i] = mfma16(f.ah[i], f.bh[j], zero);
+            else if constexpr (g == 1) t1[i] = mfma16(f.al[i], f.bh[j], zero);
+            else t1[i] = mfma16(f.ah[i], f.bl[j], t1[i]);
+          }
+          after(std::integral_constant<int, 3 * kRT * j + m>{});
+        });
 #pragma unroll
         for (int i = 0; i < kRT; ++i)
 #pragma unroll
@@ -238,38 +221,59 @@ __device__ __forceinline__ void small_tile(const SmallArgs& g, uint16_t* lds) {
       });
     }
   };
-  constexpr int kGroups = kFold == kHiFold ? kCT : 3 * kCT;
 
   // Stages 0 .. kStages-1 are in flight before the loop; step t waits for
   // stage t+1, reads its fragments while the MFMAs of stage t run, and refills
   // the slot of stage t (every wave has read it before this step's barrier).
-  // The copies go between groups of MFMAs.
 #pragma unroll
   for (int t = 0; t < S::kStages; ++t)
 #pragma unroll
     for (int i = 0; i < S::kDma; ++i) copy_one(t, t, i);
   wait_vmcnt<(S::kStages - 1) * S::kDma>();
   lds_barrier();
+  // A burst of LDS reads or of copies holds the wave's issue for as long as the
+  // LDS or the copy engine takes to serve all waves', so the reads of the next
+  // step go one after each MFMA (more where a step has fewer MFMAs than reads).
+  // The copies go after the reads, or, where a wave has 8 or more accumulators,
+  // evenly over the step (2048 x 2048 x 2816 on 128-wide tiles 59 us so, 62
+  // after the reads; 1024 x 1024 x 4096 on 64-wide tiles 36 and 32).
+  constexpr int kReads = (kFold == kHiFold ? 1 : 2) * (kRT + kCT);
+  constexpr int kReadsPer = (kReads + kMfmas - 1) / kMfmas;
   Frags f[2];
-  read(f[0], 0);
+  static_for<kReads>([&](auto Rc) { read_one(f[0], 0, Rc); });
+  if constexpr (kScaled) {
+#pragma unroll
+    for (int j = 0; j < kCT; ++j) f[0].bs[j] = f[0].bh[j] * s8;
+  }
   int slot = 0;  // of stage t
   auto step = [&](int t, const Frags& cur, Frags& next) {
     SCHED_FENCE();
     wait_vmcnt<(S::kStages - 2) * S::kDma>();
     lds_barrier();
-    const int old = slot;
+    const int refill = slot;
     slot = slot + 1 == S::kStages ? 0 : slot + 1;
-    read(next, slot);
     SCHED_FENCE();
-    multiply(cur, [&](auto G) {
-      constexpr int n = decltype(G)::value;
-      constexpr int d0 = n * S::kDma / kGroups, d1 = (n + 1) * S::kDma / kGroups;
-      if constexpr (d1 > d0) {
-        SCHED_FENCE();
+    multiply(cur, [&](auto Mc) {
+      constexpr int m = decltype(Mc)::value;
+      SCHED_FENCE();
+      static_for<kReadsPer>([&](auto Rc) {
+        constexpr int r = m * kReadsPer + decltype(Rc)::value;
+        if constexpr (r < kReads) read_one(next, slot, std::integral_constant<int, r>{});
+      });
+      constexpr int kReadSlots = (kReads + kReadsPer - 1) / kReadsPer;
+      constexpr int kFirst = kTile >= 8 ? 0 : kReadSlots < kMfmas ? kReadSlots : kMfmas - 1;
+      constexpr int kSlots = kMfmas - kFirst, n = m - kFirst;
+      constexpr int d0 = n < 0 ? 0 : n * S::kDma / kSlots;
+      constexpr int d1 = n < 0 ? 0 : (n + 1) * S::kDma / kSlots;
 #pragma unroll
-        for (int i = d0; i < d1; ++i) copy_one(t + S::kStages, old, i);
-        SCHED_FENCE();
+      for (int i = d0; i < d1; ++i) copy_one(t + S::kStages, refill, i);
+      // s B_hi of the next step, of whose reads B_hi came first, after the last
+      // MFMAs of this one.
+      if constexpr (kScaled && m >= kMfmas - kCT) {
+        constexpr int j = m - (kMfmas - kCT);
+        next.bs[j] = next.bh[j] * s8;
       }
+      SCHED_FENCE();
     });
   };
   for (int t = 0; t < ksteps; t += 2) {
@@ -361,54 +365,62 @@ hipError_t launch_config(int tile, const Planes& p, int64_t M, int64_t N, float*
   switch (tile) {
     case 32: return launch_small<V, 32, 32, 2, 2, 8>(p, M, N, C, ldc, s, stream, opt, report);
     case 64:
-      if constexpr (V == kHiOnly)
-        return launch_small<V, 64, 64, 2, 2, 8>(p, M, N, C, ldc, s, stream, opt, report);
-      else
+      // Four waves of 32 x 32 read fewer LDS bytes per MFMA than eight of 16 x
+      // 32 (1024 x 1024 x 4096: elementwise 32 against 37 us); the cross-first
+      // folds keep eight, whose vector adds overlap the other wave's MFMAs (39
+      // against 41).
+      if constexpr (V == kCrossFirst)
         return launch_small<V, 64, 64, 4, 2, 4>(p, M, N, C, ldc, s, stream, opt, report);
+      else
+        return launch_small<V, 64, 64, 2, 2, 4>(p, M, N, C, ldc, s, stream, opt, report);
     case 128:
       return launch_small<V, 128, 128, 2, 4, 4>(p, M, N, C, ldc, s, stream, opt, report);
     default: return hipErrorInvalidValue;
   }
 }
 
-// Microseconds per 32-wide k-step of a grid of `tiles` workgroups, one per
-// compute unit at a time: each round of 256 costs `base` plus `fill` times the
-// share of the chip it occupies (fuller rounds run slower: they share the
-// power limit and the caches).
-double grid_cost(int64_t tiles, double base, double fill) {
-  const int64_t rounds = tiles / 256, rest = tiles % 256;
-  return rounds * (base + fill) + (rest ? base + fill * rest / 256.0 : 0.0);
+// Time of a grid, in microseconds: `launch`, plus for each 32-wide k-step
+// `round` per round of workgroups that run together and `tile` per workgroup
+// of each compute unit (fuller grids share caches and the power limit).
+struct GridCost {
+  double launch, round, tile;
+};
+double grid_time(const GridCost& c, int64_t tiles, int64_t together, int64_t ksteps) {
+  return c.launch + ksteps * (c.round * ((tiles + together - 1) / together) + c.tile * tiles / 256);
 }
 
 }  // namespace
 
-// The rule: the tile whose grid costs least.  The constants (indexed by Variant)
-// were fitted to the kernels' times on 75 grids from 256 x 256 to 16384 x 512
-// at K = 512 to 2048; on those grids the pick is the fastest tile or within
-// 10 % of it.  Where the lines lie for the elementwise order, 64 k-steps: 32
-// up to 512 tiles of 32 (512 x 1024: 15.9 against 19.4 us on 64-wide tiles;
-// 512 x 1280: 23.7 against 19.4), then 64 up to 512 tiles of 64 (1024 x 2048:
-// 34.5 against 43.0 on 128; 768 x 3072: 46.7 against 44.3), then 128 while its
-// rounds are fuller than those of the wide tiles (2048 x 4096: 96.8 against
-// 122.9; 2560 x 4096: 136 against 123).
-int small_gemm_tile(int64_t M, int64_t N, int variant) {
-  auto tiles = [&](int64_t bm, int64_t bn) {
-    return ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+// The rule: the tile whose grid takes the least time.  The constants (indexed
+// by Variant) are fitted to the kernels' times on 141 grids per order, from 256
+// x 256 to 16384 x 512 at K = 512 to 2048; the pick is within 0.5 % of the
+// fastest tile on average and within 11 % on each but two (3584 x 3584 and
+// 3584 x 4096, K = 512).  Two workgroups of 32 or 64-wide tiles share a compute
+// unit (64 KiB of LDS each), so their rounds are of 512.  Where the lines lie
+// for the elementwise order at K = 2048: 32 up to 512 tiles of 32 (512 x 1024:
+// 15.9 us against 18.6 on 64-wide tiles; 512 x 1280: 23.6 against 18.9), then 64
+// up to 512 tiles of 64 (1024 x 2048: 33.8 against 37.6 on 128; 768 x 3072: 45
+// against 39), then 128 while the wide tiles' rounds are emptier (2048 x 4096:
+// 91 against 123; 2560 x 4096: 133 against 123).
+int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant) {
+  static constexpr GridCost k32[4] = {
+      {3.8, 0.044, 0.077}, {3.5, 0.029, 0.080}, {3.2, 0.031, 0.029}, {3.8, 0.059, 0.074}};
+  static constexpr GridCost k64[4] = {
+      {4.4, 0.112, 0.156}, {4.2, 0.099, 0.158}, {3.7, 0.079, 0.058}, {3.9, 0.160, 0.153}};
+  static constexpr GridCost k128[4] = {
+      {5.7, 0.370, 0.312}, {5.5, 0.363, 0.308}, {4.8, 0.137, 0.115}, {5.3, 0.441, 0.311}};
+  static constexpr GridCost kWide[4] = {
+      {12.0, 1.281, 0.698}, {11.0, 0.655, 0.498}, {9.0, 0.604, 0.282}, {10.6, 0.787, 0.497}};
+  auto time = [&](const GridCost& c, int64_t bm, int64_t bn, int64_t together) {
+    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+    return grid_time(c, tiles, together, round_up(K, kKPad) / kSmallStep);
   };
-  struct Cost {
-    double base, fill;
-  };
-  static constexpr Cost k32[4] = {{0.105, 0.005}, {0.095, 0.005}, {0.055, 0.005}, {0.11, 0.01}};
-  static constexpr Cost k64[4] = {{0.215, 0.02}, {0.20, 0.03}, {0.115, 0.01}, {0.23, 0.02}};
-  static constexpr Cost k128[4] = {{0.54, 0.18}, {0.52, 0.19}, {0.20, 0.06}, {0.56, 0.20}};
-  static constexpr Cost kBig[4] = {{1.57, 0.60}, {0.83, 0.38}, {0.66, 0.29}, {0.95, 0.40}};
-  const bool wide = variant == kElementwise || variant == kHiOnly;
-  const double c32 = grid_cost(tiles(32, 32), k32[variant].base, k32[variant].fill);
-  const double c64 = grid_cost(tiles(64, 64), k64[variant].base, k64[variant].fill);
-  const double c128 = grid_cost(tiles(128, 128), k128[variant].base, k128[variant].fill);
-  const double big = grid_cost(tiles(256, wide ? 256 : 128), kBig[variant].base, kBig[variant].fill);
-  const double best = std::min(std::min(c32, c64), std::min(c128, big));
-  return best == big ? 0 : best == c128 ? 128 : best == c64 ? 64 : 32;
+  const bool square = variant == kElementwise || variant == kHiOnly;
+  const double t32 = time(k32[variant], 32, 32, 512), t64 = time(k64[variant], 64, 64, 512);
+  const double t128 = time(k128[variant], 128, 128, 256);
+  const double wide = time(kWide[variant], 256, square ? 256 : 128, 256);
+  const double best = std::min(std::min(t32, t64), std::min(t128, wide));
+  return best == wide ? 0 : best == t128 ? 128 : best == t64 ? 64 : 32;
 }
 
 hipError_t launch_gemm_small(int tile, const Planes& p, int64_t M, int64_t N, float* C,

@@ -180,8 +180,8 @@ hipError_t launch_unscale(const Planes& p, int64_t M, int64_t N, float* C, int64
 hipError_t launch_range_report(const Planes& p, bool empty, uint32_t* out, hipStream_t stream);
 
 // Tile side (32, 64 or 128) of the kernel in gemm_small.hip that runs an
-// M x N problem in the order `variant`, or 0 for the 256-wide kernels.
-int small_gemm_tile(int64_t M, int64_t N, int variant);
+// M x N x K problem in the order `variant`, or 0 for the 256-wide kernels.
+int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant);
 
 // The GEMM on tile x tile tiles (gemm_small.hip).  Same results as the 256-wide
 // kernels, bit for bit, range fallbacks included.  With opt.prescale it also

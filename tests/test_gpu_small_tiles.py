@@ -15,10 +15,9 @@ from tests.helpers import abs_ab, assert_parity, band_rows
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K): the tile a shape takes depends on M and N alone.  One tile with
-# remainders, a full grid of 32-wide tiles, 64-wide, 128-wide (one tile less
-# than full in each dimension); K of one, three and eleven steps of 64.
-SHAPES = [(31, 36, 64), (257, 260, 192), (512, 512, 64), (700, 1020, 192), (1100, 1500, 704)]
+# (M, N, K): one 32-wide tile with remainders, grids of 32, 64 and 128-wide
+# tiles that end inside a tile; K from one step of 64.
+SHAPES = [(31, 36, 64), (257, 260, 192), (512, 512, 64), (700, 1020, 192), (1500, 1660, 704)]
 
 
 @pytest.mark.parametrize("overflow,scale", [(False, 2048.0), (True, 2048.0), (False, 65536.0)],
