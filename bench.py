@@ -43,24 +43,28 @@ THREE_GEMM_PEAK_TFLOPS = FP16_PEAK_TFLOPS / 3
 HBM_PEAK_GBS = 8000.0
 # The MFMA kernel that runs for each order: for the elementwise order the
 # 256 x 256 kernel that splits A in registers (where the library chooses it:
-# sgemm_cube_splits_a_in_gemm) or the one that reads the A planes (elsewhere,
-# and with --unfused); either call also launches
+# sgemm_cube_splits_a_in_gemm, N <= 3072) or the one that reads the A planes
+# (elsewhere, and with --unfused); either call also launches
 # the unscaled 256 x 128 kernel, which reads the range flag and returns at once
 # unless some |B_hi| s exceeds 65504, in which case it does the work.  For
 # termwise the 256 x 128 kernel, likewise with A split in registers where the
 # library chooses it, and with --split-b-in-gemm the same kernel splitting B
 # (and A, where the library splits A in the GEMM) itself.  The cross-terms-first
 # order has a scaled kernel and an unscaled fallback too, chosen as for the
-# elementwise order.
+# elementwise order.  The 256^3 workload runs on 32-wide tiles in every order,
+# range fallback included.
 GEMM_KERNELS = {"elementwise": "gemm_el_kernel<true, true>",
                 "elementwise_unfused": "gemm_el_kernel<true, false>",
-                "elementwise_unscaled": "gemm_n128_kernel<0, false, false>",
+                "elementwise_unscaled": "gemm_unscaled_kernel<0>",
                 "termwise": "gemm_n128_kernel<1, false, false>",
                 "termwise_fused": "gemm_n128_kernel<1, true, false>",
                 "termwise_fused_b": "gemm_n128_kernel<1, false, true>",
                 "termwise_fused_ab": "gemm_n128_kernel<1, true, true>",
                 "elementwise_cross_first": "gemm_n128_kernel<4, false, false>",
-                "elementwise_cross_first_unscaled": "gemm_n128_kernel<3, false, false>"}
+                "elementwise_cross_first_unscaled": "gemm_unscaled_kernel<3>",
+                "elementwise_small": "gemm_small_kernel<0, 32, 32, 2, 2, 8>",
+                "termwise_small": "gemm_small_kernel<1, 32, 32, 2, 2, 8>",
+                "elementwise_cross_first_small": "gemm_small_kernel<3, 32, 32, 2, 2, 8>"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gemm_traffic.json")
 
 
@@ -116,6 +120,7 @@ def kernel_source_hash() -> str:
     taken on."""
     h = hashlib.sha256()
     for rel in ("paper_2507_23387_amd/csrc/gemm.hip", "paper_2507_23387_amd/csrc/gemm_tile.hip",
+                "paper_2507_23387_amd/csrc/gemm_small.hip",
                 "paper_2507_23387_amd/csrc/gemm_common.h",
                 "paper_2507_23387_amd/csrc/internal.h"):
         with open(os.path.join(ROOT, rel), encoding="utf-8") as f:
@@ -374,7 +379,8 @@ def main():
     sh = stream.cuda_stream
 
     # A step enqueues what sgemm_cube_ws enqueues.  Where the library splits
-    # A inside the GEMM kernel (sgemm_cube_splits_a_in_gemm) that is the split
+    # A inside the GEMM kernel (sgemm_cube_splits_a_in_gemm, on the 256-wide
+    # kernels and, elementwise, up to N = 3072) that is the split
     # of B (sgemm_cube_prepare with A = NULL) and sgemm_cube_compute_a; else,
     # and with --unfused or --stages, the split of both operands
     # (sgemm_cube_prepare) and the GEMM on the tiled planes.
@@ -385,7 +391,9 @@ def main():
         print(f"--tile {args.tile}: the sweep covers the elementwise order and "
               f"{sgc.binding.TILE_CONFIGS}", file=sys.stderr)
         sys.exit(2)
+    small = max(M, N) <= 256 and not tile and not args.stages and not args.split_b_in_gemm
     fused = (not args.unfused and not args.stages and not args.prescale and not tile and
+             not small and (order != "elementwise" or N <= 3072) and
              sgc.binding.sgemm_cube_splits_a_in_gemm(M, N, K, dA.data_ptr(), K, scale,
                                                      order_code) == 1)
     split_b = args.split_b_in_gemm
@@ -514,7 +522,9 @@ def main():
     # of B that found |B_hi| s > 65504 (s > 2^15 routes there too).
     hdr = ws[:8].view(torch.int32).cpu()
     unscaled = bool(hdr[0] == hdr[1]) or scale > 32768.0
-    if order == "elementwise":
+    if small:
+        kernel_key = order + "_small"
+    elif order == "elementwise":
         if unscaled:
             kernel_key = "elementwise_unscaled"
         elif tile:

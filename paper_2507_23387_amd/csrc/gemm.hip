@@ -14,18 +14,18 @@
 //                    splits in registers (Sec. 3.3).
 //   gemm_n128_kernel 256 x 128 tiles, v_mfma_f32_16x16x32_f16: the orders
 //                    that need more than one register set -- termwise (Eq.
-//                    termwise), the unscaled elementwise fallback (range
-//                    flag set) and the cross-terms-first order (end of
-//                    Sec. 4.5), scaled and unscaled; termwise also on FP32
-//                    A split in registers (kFusedA) and on FP32 B that the
-//                    workgroup splits into its LDS planes (kFusedB).
+//                    termwise) and the scaled cross-terms-first order (end of
+//                    Sec. 4.5); termwise also on FP32 A split in registers
+//                    (kFusedA) and on FP32 B that the workgroup splits into
+//                    its LDS planes (kFusedB).
 //   gemm_hi_kernel   256 x 256 tiles: HH only, the native-FP16 baseline.
-// The tile-shape sweep of the scaled elementwise order is in gemm_tile.hip.
-// For the elementwise and cross-terms-first orders with s <= 2^15 both the
-// scaled and the unscaled kernel of the order are launched; each reads the
-// range flag first and the one that does not apply returns at once.  For s >
-// 2^15, which is not a finite FP16 value, the host launches the unscaled
-// kernel alone.
+// The tile-shape sweep of the scaled elementwise order is in gemm_tile.hip, the
+// smaller tiles and the unscaled kernels (range flag set, or s > 2^15) in
+// gemm_small.hip.  For the elementwise and cross-terms-first orders with s <=
+// 2^15 both the scaled and the unscaled kernel of the order are launched; each
+// reads the range flag first and the one that does not apply returns at once.
+// For s > 2^15, which is not a finite FP16 value, the host launches the
+// unscaled kernel alone.
 //
 // Data path.  The planes are stored as 4 KiB tiles of 128 rows x 16 k in the
 // order and swizzle the LDS wants (internal.h), so one pipeline stage (one
@@ -135,7 +135,7 @@ __device__ void split_a_planes(const float* __restrict__ A, int64_t lda, int M, 
 // v_pk_mul_f16 from s converted to FP16; it is exact because s is a power of
 // two, provided s <= 2^15 (checked on the host, which otherwise never launches
 // this kernel) and |B_hi| s <= 65504, which the split of B checks (the range
-// flag; when it is set this kernel returns at once and gemm_n128_kernel
+// flag; when it is set this kernel returns at once and gemm_unscaled_kernel
 // computes C).  Each
 // block term is summed by the MFMA together with the accumulator, with one
 // rounding, instead of being rounded to FP32 on its own first.
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_el_kernel(
   if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, tm, tn))
     tile_of<4>(blockIdx.x, tiles_m, tiles_n, tm, tn);
   if (range[0] == range[1]) {
-    // s B_hi overflows FP16: gemm_n128_kernel runs instead.  Without planes
+    // s B_hi overflows FP16: gemm_unscaled_kernel runs instead.  Without planes
     // of A (fused split), this kernel first writes them for it.
     if constexpr (kFusedA) split_a_planes(af, lda, M, K, tiles_m * kWide, Kp, a_hi, a_lo, s);
     return;
@@ -532,11 +532,6 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_hi_kernel(
 //   kTermwise (Eq. termwise): HH = A_hi B_hi, XA = A_lo B_hi, XB = A_hi B_lo
 //     accumulate over all of K (HH and XA in AGPRs, XB in VGPRs, each
 //     updated once per step) and the epilogue forms C = (HH + XA / s) + XB / s.
-//   kElementwise when the range flag is set (s B_hi overflows FP16, so the
-//     scaled 256 x 256 kernel cannot run): unscaled, blocks of one 32-wide
-//     k-step.  HH goes straight into the accumulator (VGPRs) and XA_g, XB_g
-//     into block sums started from zero; one column block later,
-//     acc = (acc + XA_g / s) + XB_g / s with two v_fma_f32 (1/s is exact).
 //   kCrossScaled (the reordered elementwise accumulation proposed at the end
 //     of Sec. 4.5), the scaled kernel of that order: per block one MFMA
 //     chain started from zero, XA_g, then XB_g, then A_hi (s B_hi), gives
@@ -545,11 +540,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_hi_kernel(
 //     2^15, range flag clear; when it is set this kernel returns at once);
 //     one column block later the accumulator, which holds s * acc, adds it
 //     with one v_add_f32, and C = (s * acc) / s.
-//   kCrossFirst, its unscaled fallback (range flag set, or s > 2^15): per
-//     block X_g = XA_g + XB_g (one MFMA chain started from zero) and HH_g
-//     (started from zero); one column block later acc = acc + (X_g / s +
-//     HH_g) with one v_fma_f32 and one add.
-// In the block-fold orders the A fragments live in AGPRs (the MFMA reads its
+// In the cross-first order the A fragments live in AGPRs (the MFMA reads its
 // A operand from there) so that the accumulators and block sums fit the
 // VGPRs; the fold of column block j runs between the MFMAs of block j+1, at
 // least 8 MFMAs after the results it reads.
@@ -560,7 +551,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_hi_kernel(
 // in registers and streams B one 16-column block at a time, one block ahead;
 // during step kt it issues 12 DMAs (B stage kt+1, then A stage kt+2; three in
 // each of blocks 0-3: spread two per block over blocks 0-5 they left the
-// block-fold orders 5-6 % slower) and reads the A fragments of step kt+1 into
+// cross-first order 5-6 % slower) and reads the A fragments of step kt+1 into
 // a second set (one or two per block, blocks 2-6).  Two barriers per step:
 // before block 2, A stage kt+1 (copied during step kt-1) has landed; before
 // block 7, B stage kt+1 has, and B stage kt is retired.  The A copies so get
@@ -619,11 +610,10 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_n128_kernel(
     const uint16_t* __restrict__ a_hi, const uint16_t* __restrict__ a_lo,
     const uint16_t* __restrict__ b_hi, const uint16_t* __restrict__ b_lo,
     const uint32_t* __restrict__ range, int Kp, int tiles_m, int tiles_n,
-    float* __restrict__ C, int64_t ldc, int M, int N, float inv_s, int unscaled_only,
+    float* __restrict__ C, int64_t ldc, int M, int N, float inv_s,
     const float* __restrict__ af, int64_t lda, float s, const float* __restrict__ bf,
     int64_t ldb) {
-  static_assert(V == kTermwise || V == kElementwise || V == kCrossFirst || V == kCrossScaled,
-                "n128 variants");
+  static_assert(V == kTermwise || V == kCrossScaled, "n128 variants");
   static_assert(!kFusedA || V == kTermwise, "the fused split of A is built for termwise only");
   static_assert(!kFusedB || V == kTermwise, "the fused split of B is built for termwise only");
   constexpr bool kFold = V != kTermwise;
@@ -642,14 +632,8 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_n128_kernel(
   static_assert(kBfBase == static_cast<int>(kTwLdsBytes), "FP32 B slots follow the planes");
   static_assert(kBfBase + kTwBfSlotBytes + 3 * 4096 + 4096 <= static_cast<int>(kTwFusedBLdsBytes) &&
                     kTwFusedBLdsBytes <= kMaxLdsBytes, "FP32 B DMAs stay in LDS");
-  if constexpr (V == kElementwise || V == kCrossFirst) {
-    // Unless the host routed the call here (unscaled_only: s is not a finite
-    // FP16 value), the scaled kernel of the order (256 x 256 elementwise,
-    // kCrossScaled) handles the case where the range flag is clear.
-    if (!unscaled_only && range[0] != range[1]) return;
-  }
   if constexpr (V == kCrossScaled) {
-    if (range[0] == range[1]) return;  // s B_hi overflows FP16: kCrossFirst runs
+    if (range[0] == range[1]) return;  // s B_hi overflows FP16: gemm_unscaled_kernel runs
   }
   extern __shared__ __align__(16) uint16_t lds[];
 
@@ -823,15 +807,15 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_n128_kernel(
     *reinterpret_cast<u32x4*>(lds + off + kBPlane) = u32x4{blw[0], blw[1], blw[2], blw[3]};
   };
 
-  // Termwise: hh, xa, xb.  Block folds: acc (= hh) and the block sums t1, t2
-  // of the current and the previous column block (index: block parity).
+  // Termwise: hh, xa, xb.  Block folds: acc (= hh) and the block sums t1 of
+  // the current and the previous column block (index: block parity).
   floatx4 hh[kRows][kCols], xa[kFold ? 1 : kRows][kFold ? 1 : kCols],
-      xb[kFold ? 1 : kRows][kFold ? 1 : kCols], t1[2][kRows], t2[2][kRows];
+      xb[kFold ? 1 : kRows][kFold ? 1 : kCols], t1[2][kRows];
 #pragma unroll
   for (int i = 0; i < kRows; ++i) {
 #pragma unroll
     for (int j = 0; j < kCols; ++j) hh[i][j] = floatx4{};
-    t1[0][i] = t1[1][i] = t2[0][i] = t2[1][i] = floatx4{};
+    t1[0][i] = t1[1][i] = floatx4{};
   }
   if constexpr (!kFold) {
 #pragma unroll
@@ -894,45 +878,20 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_n128_kernel(
   if constexpr (V == kCrossScaled) bsh[0] = pk_scale(bh[0], s2);
   lds_barrier();  // A slot 0 is refilled (stage 2) during step 0
 
-  // The fold of column block jp (block sums of parity cp) in two halves, for
-  // rows and elements q = 4 i + e in [q0, q1):
-  //   elementwise   first  acc = fl(acc + XA_g / s)       (acc holds acc + HH_g)
-  //                 second acc = fl(acc + XB_g / s)
-  //   cross-first   first  HH_g <- fl(X_g / s + HH_g)
-  //                 second acc = fl(acc + HH_g)
-  //   cross-scaled  second s acc = fl(s acc + T_g), T_g = fl(X_g + s HH_g)
-  //                 (first: nothing)
-  // One v_fma_f32 or v_add_f32 per element and half (1/s is exact).
-  auto fold_first = [&](int jp, int cp, int q0, int q1) {
+  // The fold of column block jp (block sums of parity cp) for rows and elements
+  // q = 4 i + e in [q0, q1): s acc = fl(s acc + T_g), T_g = fl(X_g + s HH_g),
+  // one v_add_f32 per element.
+  auto fold = [&](int jp, int cp, int q0, int q1) {
 #pragma unroll
-    for (int q = q0; q < q1; ++q) {
-      const int i = q >> 2, e = q & 3;
-      if constexpr (V == kElementwise)
-        hh[i][jp][e] = __builtin_fmaf(t1[cp][i][e], inv_s, hh[i][jp][e]);
-      else
-        t2[cp][i][e] = __builtin_fmaf(t1[cp][i][e], inv_s, t2[cp][i][e]);
-    }
-  };
-  auto fold_second = [&](int jp, int cp, int q0, int q1) {
-#pragma unroll
-    for (int q = q0; q < q1; ++q) {
-      const int i = q >> 2, e = q & 3;
-      if constexpr (V == kElementwise)
-        hh[i][jp][e] = __builtin_fmaf(t2[cp][i][e], inv_s, hh[i][jp][e]);
-      else if constexpr (V == kCrossScaled)
-        hh[i][jp][e] += t1[cp][i][e];
-      else
-        hh[i][jp][e] += t2[cp][i][e];
-    }
+    for (int q = q0; q < q1; ++q) hh[q >> 2][jp][q & 3] += t1[cp][q >> 2][q & 3];
   };
 
   // Column block j issues its 12 MFMAs: termwise HH(., j), XA(., j),
-  // XB(., j); elementwise HH into acc, XA_g, XB_g; cross-first HH_g, XA_g,
-  // then XB_g chained onto XA_g.  After MFMA m of a block: m = 1, 7 of blocks
-  // 2-6 read the next A fragments, m = 2, 6, 10 of blocks 0-3 issue the DMAs
-  // (the 4 of B first), and in the block-fold orders MFMAs 3-11 are each
-  // followed by 1-2 of the 16 folds of the previous column block.  DMAs
-  // complete in issue order, so a vmcnt wait retires all but the newest.
+  // XB(., j); cross-first XA_g, then XB_g and s HH_g chained onto it.  After
+  // MFMA m of a block: m = 1, 7 of blocks 2-6 read the next A fragments, m = 2,
+  // 6, 10 of blocks 0-3 issue the DMAs (the 4 of B first), and cross-first the
+  // folds of the previous column block go as noted below.  DMAs complete in
+  // issue order, so a vmcnt wait retires all but the newest.
   constexpr int kDmaPerBlock = 3, kBDmas = 4, kADmas = 8;
   // The block before which A stage kt+1 (copied during step kt-1) is waited
   // for: block 2, or block 1 with the fused split, whose reads of that stage
@@ -977,66 +936,29 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_n128_kernel(
             mfma16_acc(xa[i][j], al[i], bh[c]);
           else
             mfma16_vacc(xb[i][j], ah[i], bl[c]);
-        } else if constexpr (V == kElementwise) {
-          if constexpr (g == 0)
-            mfma16_va_acc(hh[i][j], ah[i], bh[c]);
-          else if constexpr (g == 1)
-            mfma16_va_new(t1[c][i], al[i], bh[c]);
-          else
-            mfma16_va_new(t2[c][i], ah[i], bl[c]);
-        } else if constexpr (V == kCrossScaled) {
+        } else {
           if constexpr (g == 0)
             mfma16_va_new(t1[c][i], al[i], bh[c]);
           else if constexpr (g == 1)
             mfma16_va_acc(t1[c][i], ah[i], bl[c]);
           else
             mfma16_va_acc(t1[c][i], ah[i], bsh[c]);
-        } else {
-          if constexpr (g == 0)
-            mfma16_va_new(t2[c][i], ah[i], bh[c]);
-          else if constexpr (g == 1)
-            mfma16_va_new(t1[c][i], al[i], bh[c]);
-          else
-            mfma16_va_acc(t1[c][i], ah[i], bl[c]);
         }
         SCHED_FENCE();
-        // Folds: at most three VALU operations after any MFMA (up to two
-        // overlap an MFMA for free; each further one costs its issue time).
-        // Every block sum is read at least 8 MFMAs after the MFMA that wrote
-        // it, and before the MFMA of a later block that overwrites it.
-        if constexpr (V == kElementwise) {
-          // Block jp: XA_g of row i written by its MFMA 4 + i, XB_g by 8 + i,
-          // so the first half of row i may run after MFMA m >= i here and
-          // the second after m >= 4 + i.  Both halves of the 16 elements:
-          // 3,3,3,3,2,2 per MFMA over MFMAs 0-5, then 2,2,3,3,3,3 over 6-11.
-          constexpr int f1[7] = {0, 3, 6, 9, 12, 14, 16};
-          constexpr int f2[7] = {0, 2, 4, 7, 10, 13, 16};
-          if constexpr (m < 6) fold_first(jp, c ^ 1, f1[m], f1[m + 1]);
-          else fold_second(jp, c ^ 1, f2[m - 6], f2[m - 5]);
-        } else if constexpr (V == kCrossFirst) {
-          // Block jp: X_g of row i complete after its MFMA 8 + i, HH_g after
-          // MFMA i, so the first half of row i may run after m >= 4 + i.  The
-          // second half of rows 2-3 spills into the next block's MFMAs 0-2:
-          // that block (parity cp) overwrites HH_g of row i with its MFMA i.
-          constexpr int f1[7] = {0, 3, 6, 9, 12, 15, 16};  // after MFMAs 4-9
-          constexpr int f2[6] = {0, 2, 5, 8, 11, 14};      // after MFMAs 9-11, next 0-1
-          if constexpr (m >= 4 && m <= 9) fold_first(jp, c ^ 1, f1[m - 4], f1[m - 3]);
-          if constexpr (m >= 9) fold_second(jp, c ^ 1, f2[m - 9], f2[m - 8]);
-          // The spill of block j - 2 (the same parity as this block).
-          constexpr int jpp = (j + kCols - 2) % kCols;
-          if constexpr (m == 0) fold_second(jpp, c, 8, 11);
-          if constexpr (m == 1) fold_second(jpp, c, 11, 14);
-          if constexpr (m == 2) fold_second(jpp, c, 14, 16);
-        } else if constexpr (V == kCrossScaled) {
+        // Folds: at most two VALU operations after any MFMA (they overlap it for
+        // free; each further one costs its issue time).  Every block sum is
+        // read at least 8 MFMAs after the MFMA that wrote it, and before the
+        // MFMA of a later block that overwrites it.
+        if constexpr (V == kCrossScaled) {
           // Block jp: T_g of row i is complete after its MFMA 8 + i, so its
           // fold may run after m >= 4 + i: rows 0-2 fold two elements after
           // each of MFMAs 4-9, and row 3 spills into the next block's MFMAs
           // 0-1 (that block, of parity cp, overwrites T_g of row 3 with its
           // MFMA 3).  s B_hi of the next block: two v_pk_mul_f16 after each
           // of MFMAs 10 and 11, 9 MFMAs ahead of its first use.
-          if constexpr (m >= 4 && m <= 9) fold_second(jp, c ^ 1, 2 * (m - 4), 2 * (m - 3));
+          if constexpr (m >= 4 && m <= 9) fold(jp, c ^ 1, 2 * (m - 4), 2 * (m - 3));
           constexpr int jpp = (j + kCols - 2) % kCols;
-          if constexpr (m <= 1) fold_second(jpp, c, 12 + 2 * m, 14 + 2 * m);
+          if constexpr (m <= 1) fold(jpp, c, 12 + 2 * m, 14 + 2 * m);
           if constexpr (m == 10) pk_scale_half<0>(bsh[c ^ 1], bh[c ^ 1], s2);
           if constexpr (m == 11) pk_scale_half<1>(bsh[c ^ 1], bh[c ^ 1], s2);
         }
@@ -1101,16 +1023,9 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_n128_kernel(
   }
   wait_vmcnt<0>();
   mfma_drain();
-  if constexpr (V == kElementwise) {
-    fold_first(kCols - 1, 1, 0, 4 * kRows);
-    fold_second(kCols - 1, 1, 0, 4 * kRows);
-  } else if constexpr (V == kCrossFirst) {
-    fold_second(kCols - 2, 0, 8, 4 * kRows);  // the spill of block 6
-    fold_first(kCols - 1, 1, 0, 4 * kRows);
-    fold_second(kCols - 1, 1, 0, 4 * kRows);
-  } else if constexpr (V == kCrossScaled) {
-    fold_second(kCols - 2, 0, 12, 4 * kRows);  // the spill of block 6 (row 3)
-    fold_second(kCols - 1, 1, 0, 4 * kRows);
+  if constexpr (V == kCrossScaled) {
+    fold(kCols - 2, 0, 12, 4 * kRows);  // the spill of block 6 (row 3)
+    fold(kCols - 1, 1, 0, 4 * kRows);
   }
 
   const int col0 = tn * kTwN + (lane & 15);
@@ -1119,8 +1034,6 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_n128_kernel(
   store_tile16<kRows, kCols>(C, ldc, M, N, row0, col0, full, [&](int i, int j, int r) {
     if constexpr (V == kCrossScaled) {
       return hh[i][j][r] * inv_s;
-    } else if constexpr (kFold) {
-      return hh[i][j][r];
     } else {
       return __builtin_fmaf(xb[i][j][r], inv_s, __builtin_fmaf(xa[i][j][r], inv_s, hh[i][j][r]));
     }
@@ -1159,8 +1072,7 @@ hipError_t launch_hi(const Planes& p, int64_t M, int64_t N, float* C, int64_t ld
 
 template <int V, bool kFusedA = false, bool kFusedB = false>
 hipError_t launch_n128(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc, float s,
-                       hipStream_t stream, bool unscaled_only = false,
-                       const float* A = nullptr, int64_t lda = 0, const float* B = nullptr,
+                       hipStream_t stream, const float* A = nullptr, int64_t lda = 0, const float* B = nullptr,
                        int64_t ldb = 0) {
   constexpr size_t kLds = kFusedB ? kTwFusedBLdsBytes : kTwLdsBytes;
   static std::atomic<bool> done[kMaxDevices];
@@ -1171,8 +1083,7 @@ hipError_t launch_n128(const Planes& p, int64_t M, int64_t N, float* C, int64_t 
   hipLaunchKernelGGL((gemm_n128_kernel<V, kFusedA, kFusedB>), dim3(tiles_m * tiles_n),
                      dim3(kWideThreads), kLds, stream, p.a_hi, p.a_lo, p.b_hi, p.b_lo,
                      p.range, static_cast<int>(p.Kp), tiles_m, tiles_n, C, ldc,
-                     static_cast<int>(M), static_cast<int>(N), 1.0f / s, unscaled_only ? 1 : 0,
-                     A, lda, s, B, ldb);
+                     static_cast<int>(M), static_cast<int>(N), 1.0f / s, A, lda, s, B, ldb);
   return hipGetLastError();
 }
 
@@ -1190,18 +1101,18 @@ hipError_t launch_gemm_wide(const Planes& p, int64_t M, int64_t N, float* C, int
   switch (variant) {
     case kElementwise: {
       if (!scaled_kernel_ok(scale))
-        return launch_n128<kElementwise>(p, M, N, C, ldc, scale, stream, true);
+        return launch_gemm_unscaled(p, M, N, C, ldc, scale, kElementwise, true, stream);
       const hipError_t e = launch_el<true, false>(p, M, N, C, ldc, scale, stream);
       if (e != hipSuccess) return e;
-      return launch_n128<kElementwise>(p, M, N, C, ldc, scale, stream);
+      return launch_gemm_unscaled(p, M, N, C, ldc, scale, kElementwise, false, stream);
     }
     case kTermwise: return launch_n128<kTermwise>(p, M, N, C, ldc, scale, stream);
     case kCrossFirst: {
       if (!scaled_kernel_ok(scale))
-        return launch_n128<kCrossFirst>(p, M, N, C, ldc, scale, stream, true);
+        return launch_gemm_unscaled(p, M, N, C, ldc, scale, kCrossFirst, true, stream);
       const hipError_t e = launch_n128<kCrossScaled>(p, M, N, C, ldc, scale, stream);
       if (e != hipSuccess) return e;
-      return launch_n128<kCrossFirst>(p, M, N, C, ldc, scale, stream);
+      return launch_gemm_unscaled(p, M, N, C, ldc, scale, kCrossFirst, false, stream);
     }
     case kHiOnly: return launch_hi(p, M, N, C, ldc, stream);
     default: return hipErrorInvalidValue;
@@ -1220,10 +1131,10 @@ hipError_t launch_gemm_fused_a(const Planes& p, int64_t M, int64_t N, int64_t K,
                                int variant, hipStream_t stream) {
   if (!fused_split_ok(A, lda, K, scale, variant)) return hipErrorInvalidValue;
   if (variant == kTermwise)
-    return launch_n128<kTermwise, true>(p, M, N, C, ldc, scale, stream, false, A, lda);
+    return launch_n128<kTermwise, true>(p, M, N, C, ldc, scale, stream, A, lda);
   const hipError_t e = launch_el<true, true>(p, M, N, C, ldc, scale, stream, A, lda, K);
   if (e != hipSuccess) return e;
-  return launch_n128<kElementwise>(p, M, N, C, ldc, scale, stream);
+  return launch_gemm_unscaled(p, M, N, C, ldc, scale, kElementwise, false, stream);
 }
 
 bool fused_split_b_ok(const float* B, int64_t ldb, int64_t N, int64_t K) {
@@ -1238,23 +1149,18 @@ hipError_t launch_gemm_fused_b(const Planes& p, int64_t M, int64_t N, int64_t K,
   if (!fused_split_b_ok(B, ldb, N, K)) return hipErrorInvalidValue;
   if (split_a_in_gemm) {
     if (!fused_split_ok(A, lda, K, scale, kTermwise)) return hipErrorInvalidValue;
-    return launch_n128<kTermwise, true, true>(p, M, N, C, ldc, scale, stream, false, A, lda, B,
+    return launch_n128<kTermwise, true, true>(p, M, N, C, ldc, scale, stream, A, lda, B,
                                               ldb);
   }
-  return launch_n128<kTermwise, false, true>(p, M, N, C, ldc, scale, stream, false, nullptr, 0,
+  return launch_n128<kTermwise, false, true>(p, M, N, C, ldc, scale, stream, nullptr, 0,
                                              B, ldb);
-}
-
-hipError_t launch_gemm_unscaled(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,
-                                float scale, bool only, hipStream_t stream) {
-  return launch_n128<kElementwise>(p, M, N, C, ldc, scale, stream, only);
 }
 
 hipError_t launch_gemm_stages(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,
                               float scale, int stages, hipStream_t stream) {
   if (stages < 1 || stages > 2) return hipErrorInvalidValue;
   if (!scaled_kernel_ok(scale))
-    return launch_n128<kElementwise>(p, M, N, C, ldc, scale, stream, true);
+    return launch_gemm_unscaled(p, M, N, C, ldc, scale, kElementwise, true, stream);
   hipError_t e = hipSuccess;
   switch (stages) {
     case 1: e = launch_el<false, false>(p, M, N, C, ldc, scale, stream); break;
@@ -1262,7 +1168,7 @@ hipError_t launch_gemm_stages(const Planes& p, int64_t M, int64_t N, float* C, i
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
-  return launch_n128<kElementwise>(p, M, N, C, ldc, scale, stream);
+  return launch_gemm_unscaled(p, M, N, C, ldc, scale, kElementwise, false, stream);
 }
 
 }  // namespace sgc

@@ -55,11 +55,10 @@ struct SmallShape {
   // 1 KiB copies (32 rows of one slice of one plane) per stage.
   static constexpr int kUnits = kPlanes * 2 * (kBM + kBN) / 32;
   static constexpr int kDma = kUnits / kWaves;  // per wave
-  static_assert(kBM % 32 == 0 && kBN % 32 == 0 && kPanel % kBM == 0 && kPanel % kBN == 0,
-                "tiles are whole 32-row pieces of one panel");
+  static_assert(kBM % 32 == 0 && kBN % 32 == 0, "tiles are whole 32-row pieces");
   static_assert(kWRows % 16 == 0 && kWCols % 16 == 0, "whole MFMA tiles per wave");
   static_assert(kUnits % kWaves == 0, "every wave issues the same number of copies");
-  static_assert(kStages >= 3, "the ring holds the stage read, one landing, one in flight");
+  static_assert(kStages >= 2, "the ring holds the stage multiplied, then refilled, and the one read");
   static_assert(kLdsBytes <= kMaxLdsBytes, "LDS of every kernel stays within 128 KiB");
 };
 
@@ -69,7 +68,7 @@ struct SmallArgs {
   const uint16_t* b_hi;
   const uint16_t* b_lo;
   const uint32_t* range;
-  int Kp, tiles_m, tiles_n;
+  int Mp, Np, Kp, tiles_m, tiles_n;
   float* C;
   int64_t ldc;
   int M, N;
@@ -85,7 +84,8 @@ template <class S, int kFold>
 __device__ __forceinline__ void small_tile(const SmallArgs& g, uint16_t* lds) {
   constexpr int kRT = S::kRT, kCT = S::kCT;
   int tm, tn;
-  tile_of<4>(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+  if (S::kBM < 256 || !tile_of_block(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn))
+    tile_of<4>(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w / S::kWavesN, wn = w % S::kWavesN;
@@ -106,10 +106,13 @@ __device__ __forceinline__ void small_tile(const SmallArgs& g, uint16_t* lds) {
     const int v = is_a ? u : u - kAU;
     const int per_slice = (is_a ? S::kBM : S::kBN) / 32;
     const int p = v / (2 * per_slice), sl = v / per_slice % 2, r = v % per_slice;
-    const int row0 = is_a ? tm * S::kBM : tn * S::kBN;
+    // Tiles that are not whole panels can reach past the plane's padded rows
+    // (M and N rounded up to 256): those rows' results are never stored, and
+    // their copies repeat the plane's last 32 rows.
+    const int row = min((is_a ? tm * S::kBM : tn * S::kBN) + 32 * r, (is_a ? g.Mp : g.Np) - 32);
     const uint16_t* plane = is_a ? (p ? g.a_lo : g.a_hi) : (p ? g.b_lo : g.b_hi);
-    src[i] = reinterpret_cast<const char*>(plane) + (row0 / kPanel) * panel_bytes +
-             sl * (kTileHalves * 2) + (row0 % kPanel + 32 * r) * (kSlice * 2);
+    src[i] = reinterpret_cast<const char*>(plane) + (row / kPanel) * panel_bytes +
+             sl * (kTileHalves * 2) + (row % kPanel) * (kSlice * 2);
     dst[i] = lds_base + ((is_a ? p * S::kAPlane : S::kBBase + p * S::kBPlane) +
                          (sl * (is_a ? S::kBM : S::kBN) + 32 * r) * kSlice) * 2;
   }
@@ -262,9 +265,11 @@ __device__ __forceinline__ void small_tile(const SmallArgs& g, uint16_t* lds) {
       });
       constexpr int kReadSlots = (kReads + kReadsPer - 1) / kReadsPer;
       constexpr int kFirst = kTile >= 8 ? 0 : kReadSlots < kMfmas ? kReadSlots : kMfmas - 1;
-      constexpr int kSlots = kMfmas - kFirst, n = m - kFirst;
-      constexpr int d0 = n < 0 ? 0 : n * S::kDma / kSlots;
-      constexpr int d1 = n < 0 ? 0 : (n + 1) * S::kDma / kSlots;
+      // A ring of two waits for this step's copies at the next barrier: they go
+      // into its first half.
+      constexpr int kSlots = S::kStages == 2 ? kMfmas / 2 : kMfmas - kFirst, n = m - kFirst;
+      constexpr int d0 = n < 0 || n >= kSlots ? 0 : n * S::kDma / kSlots;
+      constexpr int d1 = n < 0 || n >= kSlots ? 0 : (n + 1) * S::kDma / kSlots;
 #pragma unroll
       for (int i = d0; i < d1; ++i) copy_one(t + S::kStages, refill, i);
       // s B_hi of the next step, of whose reads B_hi came first, after the last
@@ -340,6 +345,45 @@ __global__ __launch_bounds__(64 * kWM * kWN, 1) void gemm_small_kernel(SmallArgs
   }
 }
 
+// The unscaled body alone, on 256 x 128 tiles: the fallback of the 256-wide
+// scaled kernels (gemm.hip).  Unless the host routed the call here (unscaled_only:
+// s is not a finite FP16 value) it returns at once where the range flag is
+// clear.  Two waves per SIMD, so that one's folds (32 vector operations per 12
+// MFMAs) run beside the other's MFMAs: 4096 x 4096 x 16384 elementwise 1338 us,
+// cross-first 1340, against 1395 and 1429 for one wave per SIMD with the folds
+// placed between the MFMAs by hand (8192^3: 2742 against 2780, 2727 against 2821).
+using UnscaledShape = SmallShape<256, 128, 4, 2, 2, false>;
+template <int V>
+__global__ __launch_bounds__(512, 1) void gemm_unscaled_kernel(SmallArgs g, int unscaled_only) {
+  extern __shared__ __align__(16) uint16_t lds[];
+  if (!unscaled_only && g.range[0] != g.range[1]) return;
+  small_tile<UnscaledShape, V == kElementwise ? kElUnscaled : kCrUnscaled>(g, lds);
+}
+
+template <class S>
+SmallArgs small_args(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc, float s,
+                     const RangeOpts& opt, uint32_t* report) {
+  return SmallArgs{p.a_hi, p.a_lo, p.b_hi, p.b_lo, p.range, static_cast<int>(p.Mp),
+                   static_cast<int>(p.Np), static_cast<int>(p.Kp),
+                   static_cast<int>((M + S::kBM - 1) / S::kBM),
+                   static_cast<int>((N + S::kBN - 1) / S::kBN), C, ldc, static_cast<int>(M),
+                   static_cast<int>(N), s, 1.0f / s, opt.prescale ? p.row_max : nullptr,
+                   opt.prescale ? p.col_max : nullptr, opt.exp_a, opt.exp_b, report};
+}
+
+template <int V>
+hipError_t launch_unscaled(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc, float s,
+                           bool only, hipStream_t stream) {
+  using S = UnscaledShape;
+  static std::atomic<bool> done[kMaxDevices];
+  const hipError_t attr = set_lds(&gemm_unscaled_kernel<V>, S::kLdsBytes, done);
+  if (attr != hipSuccess) return attr;
+  const SmallArgs g = small_args<S>(p, M, N, C, ldc, s, RangeOpts{}, nullptr);
+  hipLaunchKernelGGL(gemm_unscaled_kernel<V>, dim3(g.tiles_m * g.tiles_n), dim3(S::kThreads),
+                     S::kLdsBytes, stream, g, only ? 1 : 0);
+  return hipGetLastError();
+}
+
 template <int V, int kBM, int kBN, int kWM, int kWN, int kStages>
 hipError_t launch_small(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc, float s,
                         hipStream_t stream, const RangeOpts& opt, uint32_t* report) {
@@ -348,11 +392,7 @@ hipError_t launch_small(const Planes& p, int64_t M, int64_t N, float* C, int64_t
   const hipError_t attr =
       set_lds(&gemm_small_kernel<V, kBM, kBN, kWM, kWN, kStages>, S::kLdsBytes, done);
   if (attr != hipSuccess) return attr;
-  SmallArgs g{p.a_hi, p.a_lo, p.b_hi, p.b_lo, p.range, static_cast<int>(p.Kp),
-              static_cast<int>((M + kBM - 1) / kBM), static_cast<int>((N + kBN - 1) / kBN),
-              C, ldc, static_cast<int>(M), static_cast<int>(N), s, 1.0f / s,
-              opt.prescale ? p.row_max : nullptr, opt.prescale ? p.col_max : nullptr,
-              opt.exp_a, opt.exp_b, report};
+  const SmallArgs g = small_args<S>(p, M, N, C, ldc, s, opt, report);
   hipLaunchKernelGGL((gemm_small_kernel<V, kBM, kBN, kWM, kWN, kStages>),
                      dim3(g.tiles_m * g.tiles_n), dim3(S::kThreads), S::kLdsBytes, stream, g,
                      scaled_kernel_ok(s) ? 0 : 1);
@@ -373,6 +413,14 @@ hipError_t launch_config(int tile, const Planes& p, int64_t M, int64_t N, float*
         return launch_small<V, 64, 64, 4, 2, 4>(p, M, N, C, ldc, s, stream, opt, report);
       else
         return launch_small<V, 64, 64, 2, 2, 4>(p, M, N, C, ldc, s, stream, opt, report);
+    case 192:
+      // Orders of one accumulator set: eight waves of 48 x 96 fit both steps'
+      // fragments in VGPRs (four of 96 x 96 move the accumulators of the folds
+      // in and out of AGPRs: cross-first 3072 x 3072 x 2048 129 us against 98).
+      if constexpr (V == kElementwise || V == kCrossFirst)
+        return launch_small<V, 192, 192, 4, 2, 2>(p, M, N, C, ldc, s, stream, opt, report);
+      else
+        return hipErrorInvalidValue;
     case 128:
       return launch_small<V, 128, 128, 2, 4, 4>(p, M, N, C, ldc, s, stream, opt, report);
     default: return hipErrorInvalidValue;
@@ -401,7 +449,9 @@ double grid_time(const GridCost& c, int64_t tiles, int64_t together, int64_t kst
 // 15.9 us against 18.6 on 64-wide tiles; 512 x 1280: 23.6 against 18.9), then 64
 // up to 512 tiles of 64 (1024 x 2048: 33.8 against 37.6 on 128; 768 x 3072: 45
 // against 39), then 128 while the wide tiles' rounds are emptier (2048 x 4096:
-// 91 against 123; 2560 x 4096: 133 against 123).
+// 91 against 123).  192-wide tiles take the grids between 256 tiles of 128 and
+// 256 of 256 (3072 x 3072: 90 us, 118 on 128 and 115 on wide ones; 5760 x 5760
+// x 4096: 652 against 712).
 int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant) {
   static constexpr GridCost k32[4] = {
       {3.8, 0.044, 0.077}, {3.5, 0.029, 0.080}, {3.2, 0.031, 0.029}, {3.8, 0.059, 0.074}};
@@ -409,6 +459,8 @@ int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant) {
       {4.4, 0.112, 0.156}, {4.2, 0.099, 0.158}, {3.7, 0.079, 0.058}, {3.9, 0.160, 0.153}};
   static constexpr GridCost k128[4] = {
       {5.7, 0.370, 0.312}, {5.5, 0.363, 0.308}, {4.8, 0.137, 0.115}, {5.3, 0.441, 0.311}};
+  static constexpr GridCost k192[4] = {
+      {8.5, 0.732, 0.548}, {}, {}, {8.5, 0.829, 0.582}};
   static constexpr GridCost kWide[4] = {
       {12.0, 1.281, 0.698}, {11.0, 0.655, 0.498}, {9.0, 0.604, 0.282}, {10.6, 0.787, 0.497}};
   auto time = [&](const GridCost& c, int64_t bm, int64_t bn, int64_t together) {
@@ -419,8 +471,22 @@ int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant) {
   const double t32 = time(k32[variant], 32, 32, 512), t64 = time(k64[variant], 64, 64, 512);
   const double t128 = time(k128[variant], 128, 128, 256);
   const double wide = time(kWide[variant], 256, square ? 256 : 128, 256);
-  const double best = std::min(std::min(t32, t64), std::min(t128, wide));
+  double best = std::min(std::min(t32, t64), std::min(t128, wide));
+  if (variant == kElementwise || variant == kCrossFirst) {
+    const double t192 = time(k192[variant], 192, 192, 256);
+    if (t192 < best) return 192;
+  }
   return best == wide ? 0 : best == t128 ? 128 : best == t64 ? 64 : 32;
+}
+
+hipError_t launch_gemm_unscaled(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,
+                                float scale, int variant, bool only, hipStream_t stream) {
+  switch (variant) {
+    case kElementwise:
+      return launch_unscaled<kElementwise>(p, M, N, C, ldc, scale, only, stream);
+    case kCrossFirst: return launch_unscaled<kCrossFirst>(p, M, N, C, ldc, scale, only, stream);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_gemm_small(int tile, const Planes& p, int64_t M, int64_t N, float* C,

@@ -245,7 +245,8 @@ hipError_t launch_gemm_tile(const Planes& p, int64_t M, int64_t N, float* C, int
                             float scale, int tile_m, int tile_n, int block_k, int waves,
                             hipStream_t stream) {
   if (!tile_config_ok(tile_m, tile_n, block_k, waves)) return hipErrorInvalidValue;
-  if (!scaled_kernel_ok(scale)) return launch_gemm_unscaled(p, M, N, C, ldc, scale, true, stream);
+  if (!scaled_kernel_ok(scale)) 
+    return launch_gemm_unscaled(p, M, N, C, ldc, scale, kElementwise, true, stream);
   hipError_t e = hipSuccess;
   if (waves == 8)
     e = launch_tile<256, 256, 32, 1, 2, 4>(p, M, N, C, ldc, scale, stream);
@@ -260,7 +261,7 @@ hipError_t launch_gemm_tile(const Planes& p, int64_t M, int64_t N, float* C, int
   else
     e = launch_tile<128, 128, 64, 1>(p, M, N, C, ldc, scale, stream);
   if (e != hipSuccess) return e;
-  return launch_gemm_unscaled(p, M, N, C, ldc, scale, false, stream);
+  return launch_gemm_unscaled(p, M, N, C, ldc, scale, kElementwise, false, stream);
 }
 
 }  // namespace sgc

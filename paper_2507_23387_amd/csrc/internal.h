@@ -179,7 +179,7 @@ hipError_t launch_unscale(const Planes& p, int64_t M, int64_t N, float* C, int64
 // (0 when `empty`, i.e. no split ran).
 hipError_t launch_range_report(const Planes& p, bool empty, uint32_t* out, hipStream_t stream);
 
-// Tile side (32, 64 or 128) of the kernel in gemm_small.hip that runs an
+// Tile side (32, 64, 128 or 192) of the kernel in gemm_small.hip that runs an
 // M x N x K problem in the order `variant`, or 0 for the 256-wide kernels.
 int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant);
 
@@ -206,11 +206,12 @@ hipError_t launch_gemm(const Planes& p, int64_t M, int64_t N, float* C, int64_t 
 hipError_t launch_gemm_stages(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,
                               float scale, int stages, hipStream_t stream);
 
-// The unscaled elementwise kernel alone (only = true: it computes C whatever
-// the range flag says) or after a scaled kernel (only = false: it computes C
-// when the range flag is set and returns at once otherwise).
+// The unscaled kernel of the elementwise or cross-terms-first order
+// (gemm_small.hip) alone (only = true: it computes C whatever the range flag
+// says) or after a scaled kernel (only = false: it computes C when the range
+// flag is set and returns at once otherwise).
 hipError_t launch_gemm_unscaled(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,
-                                float scale, bool only, hipStream_t stream);
+                                float scale, int variant, bool only, hipStream_t stream);
 
 // The tile-shape and k-depth sweep of the scaled elementwise kernel
 // (gemm_tile.hip): tile_m x tile_n tiles of C with block_k of k per pipeline

@@ -1,4 +1,4 @@
-"""The 32, 64 and 128-wide tile kernels that the library picks for problems
+"""The 32, 64, 128 and 192-wide tile kernels that the library picks for problems
 whose 256-wide tiles leave compute units idle, at tile edges and remainders.
 
 Elementwise: bit for bit the 256 x 256 sweep kernel on the same planes (scaled
@@ -15,9 +15,12 @@ from tests.helpers import abs_ab, assert_parity, band_rows
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K): one 32-wide tile with remainders, grids of 32, 64 and 128-wide
-# tiles that end inside a tile; K from one step of 64.
-SHAPES = [(31, 36, 64), (257, 260, 192), (512, 512, 64), (700, 1020, 192), (1500, 1660, 704)]
+# (M, N, K): one 32-wide tile with remainders, grids of 32, 64, 128 and 192-wide
+# tiles that end inside a tile (the last past the planes' padded rows: 2600 lies
+# in 14 tiles of 192, 2688 rows, and pads to 2816; 2740 in 15, 2880); K from one
+# step of 64.
+SHAPES = [(31, 36, 64), (257, 260, 192), (512, 512, 64), (700, 1020, 192), (1500, 1660, 704),
+          (2777, 3000, 320)]
 
 
 @pytest.mark.parametrize("overflow,scale", [(False, 2048.0), (True, 2048.0), (False, 65536.0)],
