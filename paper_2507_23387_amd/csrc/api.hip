@@ -306,11 +306,26 @@ bool pool_alloc(void** ws, size_t need, hipMemPool_t pool, hipStream_t stream) {
   return false;
 }
 
-// Gives the kept workspace back to the pool; the caller holds w.mu.
-void release(NullWorkspace& w) {
-  if (w.ptr) (void)hipFreeAsync(w.ptr, nullptr);
+// Gives the kept workspace back to the pool; the caller holds w.mu.  False (and
+// the workspace stays) when the runtime refuses.
+bool release(NullWorkspace& w) {
+  if (w.ptr && hipFreeAsync(w.ptr, nullptr) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
   w.ptr = nullptr;
   w.bytes = 0;
+  return true;
+}
+
+// A captured stream cannot use memory freed outside its graph, and work on the
+// null stream meanwhile would end the capture.
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) == hipSuccess)
+    return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
 }
 
 int run_allocating(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
@@ -330,8 +345,8 @@ int run_allocating(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
     std::unique_lock<std::mutex> lock(kept.mu, std::try_to_lock);
     if (lock.owns_lock()) {  // else another thread is enqueueing: allocate below
       if (kept.bytes < need) {
-        release(kept);
-        if (!pool_alloc(&kept.ptr, need, pool, stream)) return SGEMM_CUBE_ERR_ALLOC;
+        if (!release(kept) || !pool_alloc(&kept.ptr, need, pool, stream))
+          return SGEMM_CUBE_ERR_ALLOC;
         kept.bytes = need;
       }
       return run(M, N, K, A, lda, B, ldb, C, ldc, scale, variant, kept.ptr, stream);
@@ -339,10 +354,10 @@ int run_allocating(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
   }
   void* ws = nullptr;
   if (!pool_alloc(&ws, need, pool, stream)) {
+    if (capturing(stream)) return SGEMM_CUBE_ERR_ALLOC;
     {
       std::lock_guard<std::mutex> lock(kept.mu);
-      if (!kept.ptr) return SGEMM_CUBE_ERR_ALLOC;
-      release(kept);
+      if (!kept.ptr || !release(kept)) return SGEMM_CUBE_ERR_ALLOC;
     }
     if (!pool_alloc(&ws, need, pool, stream)) return SGEMM_CUBE_ERR_ALLOC;
   }
