@@ -26,6 +26,7 @@
 // x 2816.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 
 #include "gemm_common.h"
 
@@ -388,6 +389,7 @@ template <int V, int kBM, int kBN, int kWM, int kWN, int kStages>
 hipError_t launch_small(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc, float s,
                         hipStream_t stream, const RangeOpts& opt, uint32_t* report) {
   using S = SmallShape<kBM, kBN, kWM, kWN, kStages, V == kHiOnly>;
+  static_assert(S::kThreads == small_tile_threads(kBM, V), "the rule counts these threads");
   static std::atomic<bool> done[kMaxDevices];
   const hipError_t attr =
       set_lds(&gemm_small_kernel<V, kBM, kBN, kWM, kWN, kStages>, S::kLdsBytes, done);
@@ -465,6 +467,11 @@ int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant) {
       {12.0, 1.281, 0.698}, {11.0, 0.655, 0.498}, {9.0, 0.604, 0.282}, {10.6, 0.787, 0.497}};
   auto time = [&](const GridCost& c, int64_t bm, int64_t bn, int64_t together) {
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+    // A grid dimension holds less than 2^32 threads, which 32-wide tiles reach
+    // at M = 2^29 (137 GB of planes at K <= 64); the 256-wide kernels have room
+    // for every problem whose C fits a device.
+    if (bm < 256 && tiles * small_tile_threads(static_cast<int>(bm), variant) > UINT32_MAX)
+      return HUGE_VAL;
     return grid_time(c, tiles, together, round_up(K, kKPad) / kSmallStep);
   };
   const bool square = variant == kElementwise || variant == kHiOnly;

@@ -180,8 +180,14 @@ hipError_t launch_unscale(const Planes& p, int64_t M, int64_t N, float* C, int64
 hipError_t launch_range_report(const Planes& p, bool empty, uint32_t* out, hipStream_t stream);
 
 // Tile side (32, 64, 128 or 192) of the kernel in gemm_small.hip that runs an
-// M x N x K problem in the order `variant`, or 0 for the 256-wide kernels.
+// M x N x K problem in the order `variant`, or 0 for the 256-wide kernels.  A
+// tile's grid holds less than 2^32 threads.
 int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant);
+
+// Threads per workgroup of that kernel.
+constexpr int small_tile_threads(int tile, int variant) {
+  return tile == 32 || (tile == 64 && variant != kCrossFirst) ? 256 : 512;
+}
 
 // The GEMM on tile x tile tiles (gemm_small.hip).  Same results as the 256-wide
 // kernels, bit for bit, range fallbacks included.  With opt.prescale it also

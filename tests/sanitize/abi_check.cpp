@@ -4,7 +4,8 @@
 // are the production ones).
 //
 //   abi_check cpu   argument validation, sizes, names and the split query:
-//                   paths that return before any device work (no GPU needed)
+//                   paths that return before any device work (no GPU needed),
+//                   and the grids of the GEMM's tile rule
 //   abi_check gpu   the above, then small problems through every entry point
 //                   on the current device, results checked against an FP64
 //                   GEMM of the same FP32 inputs within 4 K 2^-24 (|A||B|)_ij
@@ -23,6 +24,7 @@
 #include <string>
 #include <vector>
 
+#include "internal.h"
 #include "sgemm_cube.h"
 
 namespace {
@@ -127,6 +129,28 @@ void check_validation() {
   for (int st = -1; st <= 5; ++st) CHECK(sgemm_cube_status_string(st) != nullptr);
   CHECK(std::string(sgemm_cube_status_string(SGEMM_CUBE_ERR_ALLOC)) == "SGEMM_CUBE_ERR_ALLOC");
   CHECK(sgemm_cube_workspace_size(0, 4, 4, 0) == 0);
+}
+
+// The grid of every tile that the rule picks holds less than 2^32 threads, up
+// to the largest M (2^30) and N (65535 panels of 128).
+void check_tile_rule() {
+  const int64_t max_m = int64_t{1} << 30, max_n = int64_t{65535} * 128;
+  for (int variant : {sgc::kElementwise, sgc::kTermwise, sgc::kHiOnly, sgc::kCrossFirst})
+    for (int64_t K : {1, 64, 2048, 1 << 20})
+      for (int64_t m = 1; m <= max_m; m *= 2)
+        for (int64_t n = 1; n <= max_n; n = n < max_n && 2 * n > max_n ? max_n : 2 * n)
+          for (int64_t M : {m - 1, m, m + 1})
+            for (int64_t N : {n - 1, n, n + 1}) {
+              if (M < 1 || M > max_m || N < 1 || N > max_n) continue;
+              const int tile = sgc::small_gemm_tile(M, N, K, variant);
+              if (tile == 0) continue;
+              const int64_t tiles = ((M + tile - 1) / tile) * ((N + tile - 1) / tile);
+              if (tiles * sgc::small_tile_threads(tile, variant) > INT64_C(0xffffffff)) {
+                std::fprintf(stderr, "variant %d: %lldx%lldx%lld picks %d-wide tiles\n", variant,
+                             (long long)M, (long long)N, (long long)K, tile);
+                ++failures;
+              }
+            }
 }
 
 // ---------------------------------------------------------------- GPU part
@@ -283,6 +307,7 @@ void check_gpu(hipStream_t s) {
 int main(int argc, char** argv) {
   const bool gpu = argc > 1 && std::strcmp(argv[1], "gpu") == 0;
   check_validation();
+  check_tile_rule();
   if (gpu) {
     int n = 0;
     CHECK(hipGetDeviceCount(&n) == hipSuccess && n > 0);
