@@ -287,7 +287,7 @@ int get_pool(hipMemPool_t* out, int* device) {
 // stream-ordered allocation.  A host thread holds `mu` while it enqueues one
 // call: the kernels of two calls must not interleave on the stream.  At most
 // kNullWorkspaceMax bytes per device are kept (a larger call allocates its
-// own), and they go back to the pool when an allocation fails.
+// own), and they go back to the pool when device memory runs out.
 struct NullWorkspace {
   std::mutex mu;
   void* ptr = nullptr;
@@ -298,18 +298,47 @@ constexpr size_t kNullWorkspaceMax = size_t{1} << 30;
 
 // Stream-ordered allocation from the pool; on failure clears the runtime's last
 // error, so that it is not reported by the launch check of a later call on this
-// thread.
-bool pool_alloc(void** ws, size_t need, hipMemPool_t pool, hipStream_t stream) {
+// thread.  hipErrorOutOfMemory says that memory ran out; the runtime refuses with
+// other errors too, for instance where an open capture forbids the call.
+hipError_t pool_alloc(void** ws, size_t need, hipMemPool_t pool, hipStream_t stream) {
   *ws = nullptr;
-  if (hipMallocFromPoolAsync(ws, need, pool, stream) == hipSuccess && *ws) return true;
-  (void)hipGetLastError();
-  return false;
+  hipError_t e = hipMallocFromPoolAsync(ws, need, pool, stream);
+  if (e == hipSuccess && !*ws) e = hipErrorOutOfMemory;
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
 }
 
-// Gives the kept workspace back to the pool; the caller holds w.mu.  False (and
-// the workspace stays) when the runtime refuses.
-bool release(NullWorkspace& w) {
-  if (w.ptr && hipFreeAsync(w.ptr, nullptr) != hipSuccess) {
+// Gives the kept workspace back to the pool for a call on `stream`; the caller
+// holds w.mu.  False (and the workspace stays) when the runtime refuses.  Work
+// on the null stream ends a capture that any thread has open on a blocking
+// stream, so only a call on the null stream frees it there.  Another stream's
+// call takes a blocking stream of its own, which the runtime orders after all
+// earlier work of the null stream, waits for a fill on it, and frees the then
+// idle workspace on it, with this thread in the relaxed capture mode: in the
+// default mode the wait itself ends a capture that another thread has open.
+// While a blocking stream is captured the fill is refused, hence the call too.
+bool release(NullWorkspace& w, hipStream_t stream) {
+  bool ok = true;
+  if (w.ptr && stream == nullptr) {
+    ok = hipFreeAsync(w.ptr, nullptr) == hipSuccess;
+  } else if (w.ptr) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    hipStream_t own = nullptr;
+    ok = hipStreamCreateWithFlags(&own, hipStreamDefault) == hipSuccess;
+    if (ok) {
+      ok = launch_zero(1, 1, static_cast<float*>(w.ptr), 1, own) == hipSuccess &&
+           hipStreamSynchronize(own) == hipSuccess && hipFreeAsync(w.ptr, own) == hipSuccess;
+      // The free is done, so that the pool can hand the memory to any stream.
+      if (ok) (void)hipStreamSynchronize(own);
+      (void)hipStreamDestroy(own);
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  if (!ok) {
     (void)hipGetLastError();
     return false;
   }
@@ -318,8 +347,9 @@ bool release(NullWorkspace& w) {
   return true;
 }
 
-// A captured stream cannot use memory freed outside its graph, and work on the
-// null stream meanwhile would end the capture.
+// Whether `stream` is being captured; for the null stream, whether work on it
+// would join a capture that is open on some blocking stream (the runtime
+// reports that as an error of the query).
 bool capturing(hipStream_t stream) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &status) == hipSuccess)
@@ -341,26 +371,33 @@ int run_allocating(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
     return st;
   }
   NullWorkspace& kept = g_null_ws[dev];
-  if (stream == nullptr && need <= kNullWorkspaceMax) {
+  void* ws = nullptr;
+  if (stream == nullptr && need <= kNullWorkspaceMax && !capturing(stream)) {
     std::unique_lock<std::mutex> lock(kept.mu, std::try_to_lock);
     if (lock.owns_lock()) {  // else another thread is enqueueing: allocate below
       if (kept.bytes < need) {
-        if (!release(kept) || !pool_alloc(&kept.ptr, need, pool, stream))
+        // Allocate first: where an open capture forbids that, nothing is freed.
+        hipError_t e = pool_alloc(&ws, need, pool, stream);
+        if (e == hipErrorOutOfMemory && kept.ptr && release(kept, stream))
+          e = pool_alloc(&ws, need, pool, stream);
+        if (e != hipSuccess) return SGEMM_CUBE_ERR_ALLOC;
+        if (!release(kept, stream)) {
+          (void)hipFreeAsync(ws, stream);
+          (void)hipGetLastError();
           return SGEMM_CUBE_ERR_ALLOC;
+        }
+        kept.ptr = ws;
         kept.bytes = need;
       }
       return run(M, N, K, A, lda, B, ldb, C, ldc, scale, variant, kept.ptr, stream);
     }
   }
-  void* ws = nullptr;
-  if (!pool_alloc(&ws, need, pool, stream)) {
-    if (capturing(stream)) return SGEMM_CUBE_ERR_ALLOC;
-    {
-      std::lock_guard<std::mutex> lock(kept.mu);
-      if (!kept.ptr || !release(kept)) return SGEMM_CUBE_ERR_ALLOC;
-    }
-    if (!pool_alloc(&ws, need, pool, stream)) return SGEMM_CUBE_ERR_ALLOC;
+  hipError_t e = pool_alloc(&ws, need, pool, stream);
+  if (e == hipErrorOutOfMemory && !capturing(stream)) {
+    std::lock_guard<std::mutex> lock(kept.mu);
+    if (kept.ptr && release(kept, stream)) e = pool_alloc(&ws, need, pool, stream);
   }
+  if (e != hipSuccess) return SGEMM_CUBE_ERR_ALLOC;
   st = run(M, N, K, A, lda, B, ldb, C, ldc, scale, variant, ws, stream);
   if (hipFreeAsync(ws, stream) != hipSuccess && st == SGEMM_CUBE_OK) st = SGEMM_CUBE_ERR_HIP;
   return st;

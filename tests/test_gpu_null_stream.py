@@ -1,7 +1,12 @@
 """The workspace that the null stream keeps between calls of sgemm_cube and
 sgemm_cube_hgemm: calls queued back to back with sizes that grow and shrink
 (nothing waits between them), and from several host threads at once, each give
-the bits of sgemm_cube_ws with a workspace of its own."""
+the bits of sgemm_cube_ws with a workspace of its own.  In child processes
+(tests/kept_workspace_child.py): what calls on other streams do to it when
+memory has run out, and when another thread has a capture open."""
+import os
+import subprocess
+import sys
 import threading
 
 import pytest
@@ -70,3 +75,13 @@ def test_threads_on_the_null_stream(gpu):
         assert len(cs) == 20
         for c in cs:
             assert torch.equal(c.view(torch.int32), want[i].view(torch.int32)), SHAPES[i]
+
+
+@pytest.mark.parametrize("scenario", ["memory", "capture", "capture_blocking"])
+def test_kept_workspace_and_other_streams(gpu, scenario):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    log(f"kept workspace: {scenario} (child process)")
+    r = subprocess.run([sys.executable, "-u", os.path.join(root, "tests", "kept_workspace_child.py"),
+                        scenario], capture_output=True, text=True, timeout=100, cwd=root)
+    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
+    assert r.stdout.strip().endswith("ok")
