@@ -6,6 +6,9 @@
 //   abi_check cpu   argument validation, sizes, names and the split query:
 //                   paths that return before any device work (no GPU needed),
 //                   and the grids of the GEMM's tile rule
+//   abi_check rule FILE
+//                   the tile rule's picks against the measured times in FILE
+//                   (profiles/tile_rule_grids.csv)
 //   abi_check gpu   the above, then small problems through every entry point
 //                   on the current device, results checked against an FP64
 //                   GEMM of the same FP32 inputs within 4 K 2^-24 (|A||B|)_ij
@@ -151,6 +154,61 @@ void check_tile_rule() {
                 ++failures;
               }
             }
+}
+
+// The rule's picks against measured times: per order the GEMM on the picked tile
+// is within 1 % of the fastest tile's on average, and more than 5 % slower than
+// on the 256-wide kernels (which have run these sizes too) on less than 0.2 % of
+// the problems.
+void check_tile_picks(const char* file) {
+  const struct {
+    const char* name;
+    int variant, column, tiles;  // columns: 256-wide, then 32, 64, 128 (and 192)
+  } orders[4] = {{"elementwise", sgc::kElementwise, 3, 5},
+                 {"termwise", sgc::kTermwise, 8, 4},
+                 {"baseline", sgc::kHiOnly, 12, 4},
+                 {"cross-first", sgc::kCrossFirst, 16, 5}};
+  const int side[5] = {0, 32, 64, 128, 192};
+  double loss[4] = {0, 0, 0, 0};
+  int count = 0, slower[4] = {0, 0, 0, 0};
+  std::FILE* f = std::fopen(file, "r");
+  CHECK(f != nullptr);
+  if (!f) return;
+  char line[512];
+  while (std::fgets(line, sizeof line, f)) {
+    if (line[0] < '0' || line[0] > '9') continue;  // heading
+    std::vector<std::string> field(1);
+    for (const char* c = line; *c && *c != '\n'; ++c) {
+      if (*c == ',')
+        field.emplace_back();
+      else
+        field.back() += *c;
+    }
+    CHECK(field.size() == 21);
+    if (field.size() != 21) break;
+    ++count;
+    for (int o = 0; o < 4; ++o) {
+      const int pick = sgc::small_gemm_tile(std::stoll(field[0]), std::stoll(field[1]),
+                                            std::stoll(field[2]), orders[o].variant);
+      double best = HUGE_VAL, picked = HUGE_VAL;
+      for (int i = 0; i < orders[o].tiles; ++i) {
+        const std::string& t = field[orders[o].column + i];
+        if (t.empty()) continue;
+        best = std::fmin(best, std::stod(t));
+        if (side[i] == pick) picked = std::stod(t);
+      }
+      CHECK(picked < HUGE_VAL);  // else the pick was too slow to be measured
+      loss[o] += picked / best - 1;
+      slower[o] += picked > 1.05 * std::stod(field[orders[o].column]);
+    }
+  }
+  std::fclose(f);
+  CHECK(count > 1000);
+  for (int o = 0; o < 4; ++o) {
+    std::printf("%s: %d problems, %.4f slower than the fastest tile, %d slower than wide\n",
+                orders[o].name, count, loss[o] / count, slower[o]);
+    CHECK(loss[o] / count < 0.01 && slower[o] < 0.002 * count);
+  }
 }
 
 // ---------------------------------------------------------------- GPU part
@@ -306,8 +364,10 @@ void check_gpu(hipStream_t s) {
 
 int main(int argc, char** argv) {
   const bool gpu = argc > 1 && std::strcmp(argv[1], "gpu") == 0;
+  const bool rule = argc > 2 && std::strcmp(argv[1], "rule") == 0;
   check_validation();
   check_tile_rule();
+  if (rule) check_tile_picks(argv[2]);
   if (gpu) {
     int n = 0;
     CHECK(hipGetDeviceCount(&n) == hipSuccess && n > 0);
@@ -324,6 +384,6 @@ int main(int argc, char** argv) {
     std::fprintf(stderr, "%d checks failed\n", failures);
     return 1;
   }
-  std::printf("abi_check %s: all checks passed\n", gpu ? "gpu" : "cpu");
+  std::printf("abi_check %s: all checks passed\n", gpu ? "gpu" : rule ? "rule" : "cpu");
   return 0;
 }

@@ -48,3 +48,6 @@ def test_abi_host_code_under_asan_ubsan(tmp_path):
     exe = hip_build.build_sanitized(out_dir=str(tmp_path))
     out = _run([exe, "cpu"], timeout=120)
     assert "abi_check cpu: all checks passed" in out
+    # The GEMM's tile rule against the measured times it was fitted to.
+    out = _run([exe, "rule", os.path.join(ROOT, "profiles", "tile_rule_grids.csv")], timeout=120)
+    assert "abi_check rule: all checks passed" in out
