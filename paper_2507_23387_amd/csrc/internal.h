@@ -57,13 +57,15 @@ __device__ __forceinline__ void split_value(float a, float s, uint16_t& hi, uint
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// 16-byte store of a plane chunk.  A plain store: the GEMM reads the planes back
-// at once, from the last-level cache where they fit.  Non-temporal stores send
-// them past it: 1024 x 1024 x 16384 termwise took 202 us a call with them and
-// 152 without, 48 x 4096 x 4096 21.3 and 18.5, 4096^3 termwise 340 and 332,
-// 8192^3 (planes of twice the cache) 2241 and 2232.
+// 16-byte store of a plane chunk: plain, so that the GEMM reads the planes back
+// from the last-level cache, or kStream (non-temporal), past that cache.
+// launch_split chooses by the planes' size and has both sides' times.
+template <bool kStream = false>
 __device__ __forceinline__ void store_chunk(uint16_t* p, u32x4 v) {
-  *reinterpret_cast<u32x4*>(p) = v;
+  if constexpr (kStream)
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
+  else
+    *reinterpret_cast<u32x4*>(p) = v;
 }
 
 // The split of eight consecutive values into packed hi and lo words.

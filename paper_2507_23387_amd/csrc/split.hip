@@ -13,6 +13,7 @@
 // All split kernels are HBM-bound elementwise passes: 4 B read and 4 B
 // written (hi + lo) per element.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -133,7 +134,7 @@ struct SplitArgs {
 // consecutive k of rows l / 16 and l / 16 + 16, so each row is read as one
 // 512-byte piece, and the 16-byte chunks a store instruction writes fill 8
 // whole 128-byte lines (4 rows x 32 bytes of one tile each).
-template <bool kPre, bool kReport, bool kLo>
+template <bool kPre, bool kReport, bool kLo, bool kStream>
 __device__ __forceinline__ void split_a_block(const SplitArgs& g, uint32_t block) {
   const int lane = threadIdx.x & 63;
   const uint32_t kblocks = static_cast<uint32_t>((g.Kp + 127) / 128);
@@ -173,8 +174,8 @@ __device__ __forceinline__ void split_a_block(const SplitArgs& g, uint32_t block
       }
     }
     const int64_t idx = tiled_index(m, k0, g.Kp);
-    store_chunk(g.a_hi + idx, hv);
-    if constexpr (kLo) store_chunk(g.a_lo + idx, lv);
+    store_chunk<kStream>(g.a_hi + idx, hv);
+    if constexpr (kLo) store_chunk<kStream>(g.a_lo + idx, lv);
   }
   if constexpr (kReport) report_classes(cls, g.range, kWordAClass, g.a_stamp);
 }
@@ -186,7 +187,7 @@ __device__ __forceinline__ void split_a_block(const SplitArgs& g, uint32_t block
 // thread t then writes chunk t of both tiles of both planes (4 KiB contiguous
 // per tile).  It also stamps the range flag (see launch_split) when some
 // |B_hi| s > 65504, the largest finite FP16 value.
-template <bool kPre, bool kReport, bool kLo>
+template <bool kPre, bool kReport, bool kLo, bool kStream>
 __device__ __forceinline__ void split_b_block(const SplitArgs& g, uint32_t block) {
   constexpr int kK = 2 * kSlice;
   constexpr int kPitch = kK / 2 + 4;  // words per n row; 16-byte aligned rows
@@ -242,9 +243,9 @@ __device__ __forceinline__ void split_b_block(const SplitArgs& g, uint32_t block
 #pragma unroll
   for (int sl = 0; sl < kK / kSlice; ++sl) {
     const int64_t base = (panel * (g.Kp / kSlice) + kblock * (kK / kSlice) + sl) * kTileHalves + t * 8;
-    store_chunk(g.b_hi + base, *reinterpret_cast<const u32x4*>(ph + r * kPitch + sl * 8 + c * 4));
+    store_chunk<kStream>(g.b_hi + base, *reinterpret_cast<const u32x4*>(ph + r * kPitch + sl * 8 + c * 4));
     if constexpr (kLo)
-      store_chunk(g.b_lo + base, *reinterpret_cast<const u32x4*>(pl + r * kPitch + sl * 8 + c * 4));
+      store_chunk<kStream>(g.b_lo + base, *reinterpret_cast<const u32x4*>(pl + r * kPitch + sl * 8 + c * 4));
   }
 }
 
@@ -253,12 +254,12 @@ __device__ __forceinline__ void split_b_block(const SplitArgs& g, uint32_t block
 // below about 10 MB a launch, 4 us, is all it costs, hence one for both
 // operands (256^3: 8.7 to 5.0 us).  2777 x 3001 x 1531, whose rows have no
 // 16-byte alignment: 24.2 us with scalar loads in two launches, 12.6 so.
-template <bool kPre, bool kReport, bool kLo>
+template <bool kPre, bool kReport, bool kLo, bool kStream>
 __global__ __launch_bounds__(256) void split_tiled_kernel(SplitArgs g) {
   uint32_t b = blockIdx.x;
-  for (; b < g.a_blocks; b += gridDim.x) split_a_block<kPre, kReport, kLo>(g, b);
+  for (; b < g.a_blocks; b += gridDim.x) split_a_block<kPre, kReport, kLo, kStream>(g, b);
   for (; b < g.blocks; b += gridDim.x) {
-    split_b_block<kPre, kReport, kLo>(g, b - g.a_blocks);
+    split_b_block<kPre, kReport, kLo, kStream>(g, b - g.a_blocks);
     __syncthreads();  // this block's LDS words are read before the next block's are written
   }
 }
@@ -307,7 +308,7 @@ hipError_t launch_split(const Planes& p, int64_t M, int64_t N, int64_t K, const 
   g.Kp = p.Kp;
   g.K = K;
   const bool padded = what == kSplitPadded;
-  int64_t a_blocks = 0, b_blocks = 0;
+  int64_t a_rows = 0, b_rows = 0, a_blocks = 0, b_blocks = 0;
   if (B) {
     // A block that sees |B_hi| s > 65504 writes range[kWordBOverflow] = stamp,
     // every block range[kWordBStamp] = stamp, so the two words are equal
@@ -316,32 +317,54 @@ hipError_t launch_split(const Planes& p, int64_t M, int64_t N, int64_t K, const 
     g.B = B, g.ldb = ldb, g.N = N;
     g.b_hi = p.b_hi, g.b_lo = p.b_lo;
     g.col_max = p.col_max, g.exp_b = opt.exp_b, g.b_stamp = b_stamp;
-    b_blocks = p.Kp / (2 * kSlice) * ((padded ? p.Np : round_up(N, kPanel)) / kPanel);
+    b_rows = padded ? p.Np : round_up(N, kPanel);
+    b_blocks = p.Kp / (2 * kSlice) * (b_rows / kPanel);
   }
   if (A) {
     g.A = A, g.lda = lda, g.M = M;
     g.a_hi = p.a_hi, g.a_lo = p.a_lo;
     g.row_max = p.row_max, g.exp_a = opt.exp_a, g.a_stamp = a_stamp;
-    a_blocks = (p.Kp + 127) / 128 * ((padded ? p.Mp : round_up(M, kABlockRows)) / kABlockRows);
+    a_rows = padded ? p.Mp : round_up(M, kABlockRows);
+    a_blocks = (p.Kp + 127) / 128 * (a_rows / kABlockRows);
   }
   // 2^32 blocks are at least 2^43 planes' bytes, more than any device holds.
   const int64_t blocks = a_blocks + b_blocks;
   if (blocks > UINT32_MAX) return hipErrorInvalidValue;
   g.a_blocks = static_cast<uint32_t>(a_blocks);
   g.blocks = static_cast<uint32_t>(blocks);
+  // Non-temporal stores for planes that the 256 MiB last-level cache cannot hold
+  // until they are read: above 256 MiB where the GEMM follows at once, above 128
+  // MiB for planes that outlive the call.  Plain against non-temporal, us: the
+  // split of B of 64 x 8192 x 8192 (256 MiB) 107 and 84, of 4096 x 4096 x 12288
+  // (192) 82 and 67, of 64 x 8192 x 4096 (128) 46 and 45, but with the call that
+  // reads it 81 and 90; whole calls of 64 x 8192 x 8192 (258) 185 and 180, 4096 x
+  // 4096 x 8192 (256) 613 and 621, 1024 x 1024 x 16384 (128) 153 and 195, 48 x 4096
+  // x 4096 (64) 43 and 53; 8192^3 and 4096 x 4096 x 16384 (512) the same within 1 %.
+  const int64_t bytes = (a_rows + b_rows) * p.Kp * (what == kSplitHigh ? 2 : 4);
+  const bool past_cache = bytes > (padded ? int64_t{128} << 20 : int64_t{256} << 20);
   // At most 2^22 workgroups (a grid dimension holds less than 2^32 threads);
   // past that each takes several blocks.
   const dim3 grid(std::min(g.blocks, 1u << 22));
+  auto launch = [&](auto pre, auto report, auto lo) {
+    if (past_cache)
+      hipLaunchKernelGGL((split_tiled_kernel<pre.value, report.value, lo.value, true>), grid,
+                         dim3(256), 0, stream, g);
+    else
+      hipLaunchKernelGGL((split_tiled_kernel<pre.value, report.value, lo.value, false>), grid,
+                         dim3(256), 0, stream, g);
+  };
+  const std::true_type yes;
+  const std::false_type no;
   if (what == kSplitHigh)
-    hipLaunchKernelGGL((split_tiled_kernel<false, false, false>), grid, dim3(256), 0, stream, g);
+    launch(no, no, no);
   else if (opt.prescale && opt.report)
-    hipLaunchKernelGGL((split_tiled_kernel<true, true, true>), grid, dim3(256), 0, stream, g);
+    launch(yes, yes, yes);
   else if (opt.prescale)
-    hipLaunchKernelGGL((split_tiled_kernel<true, false, true>), grid, dim3(256), 0, stream, g);
+    launch(yes, no, yes);
   else if (opt.report)
-    hipLaunchKernelGGL((split_tiled_kernel<false, true, true>), grid, dim3(256), 0, stream, g);
+    launch(no, yes, yes);
   else
-    hipLaunchKernelGGL((split_tiled_kernel<false, false, true>), grid, dim3(256), 0, stream, g);
+    launch(no, no, yes);
   return hipGetLastError();
 }
 
