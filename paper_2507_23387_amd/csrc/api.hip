@@ -171,7 +171,7 @@ bool splits_a_in_gemm(int64_t N, const float* A, int64_t lda, int64_t K, float s
 bool gemm_reads_fp32_a(int64_t M, int64_t N, const float* A, int64_t lda, int64_t K, float scale,
                        int variant) {
   return splits_a_in_gemm(N, A, lda, K, scale, variant) && N <= kWideFusedMaxN &&
-         small_gemm_tile(M, N, K, variant) == 0;
+         small_gemm_tile(M, N, K, variant, !scaled_kernel_ok(scale)) == 0;
 }
 
 // GEMM from FP32 A and a workspace whose B planes are prepared: the 256-wide
@@ -230,7 +230,7 @@ int run(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const floa
   if (launch_split(p, M, N, K, A, lda, B, ldb, scale, opt, a_stamp, b_stamp,
                    variant == kHiOnly ? kSplitHigh : kSplitRows, stream) != hipSuccess)
     return SGEMM_CUBE_ERR_HIP;
-  if (const int tile = small_gemm_tile(M, N, K, variant))
+  if (const int tile = small_gemm_tile(M, N, K, variant, !scaled_kernel_ok(scale)))
     return launch_gemm_small(tile, p, M, N, C, ldc, scale, variant, stream, opt, report) ==
                    hipSuccess
                ? SGEMM_CUBE_OK

@@ -1091,7 +1091,7 @@ hipError_t launch_n128(const Planes& p, int64_t M, int64_t N, float* C, int64_t 
 
 hipError_t launch_gemm(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,
                        float scale, int variant, hipStream_t stream) {
-  if (const int tile = small_gemm_tile(M, N, p.Kp, variant))
+  if (const int tile = small_gemm_tile(M, N, p.Kp, variant, !scaled_kernel_ok(scale)))
     return launch_gemm_small(tile, p, M, N, C, ldc, scale, variant, stream);
   return launch_gemm_wide(p, M, N, C, ldc, scale, variant, stream);
 }

@@ -454,7 +454,12 @@ double grid_time(const GridCost& c, int64_t tiles, int64_t together, int64_t kst
 // kernels, most of them where those fill a round or two at small K (termwise 1024
 // x 8192 x 512: 33-35 us on 128-wide tiles, 29-30).  What is left is mostly
 // operand traffic, which the model leaves out (62 x 8118 x 4096 elementwise: 52
-// us on 32-wide tiles, 30 on 64).
+// us on 32-wide tiles, 30 on 64).  The fifth constants are those of the unscaled
+// elementwise body, for s > 2^15: its folds make 64-wide tiles, of one wave per
+// SIMD, half again as slow (762 x 5771 x 2048: 105 us on them, 80 on 256 x 128);
+// with the others' constants 124 of 1666 problems ran more than 5 % slower than
+// on the 256-wide kernel, now 1.  A call whose range flag is set runs the same
+// body on the tile picked for the scaled one.
 // Two workgroups of 32 or 64-wide tiles share a compute unit (64 KiB of LDS
 // each), so their rounds are of 512.  Where the lines lie for the elementwise
 // order at K = 2048: 32 up to 512 tiles of 32 (512 x 1024: 15.9 us against 18.6
@@ -464,25 +469,33 @@ double grid_time(const GridCost& c, int64_t tiles, int64_t together, int64_t kst
 // 192-wide tiles take the grids between 256 tiles of 128 and 256 of 256 (3072 x
 // 3072: 90 us, 118 on 128 and 115 on wide ones; 5760 x 5760 x 4096: 652 against
 // 712).
-int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant) {
-  static constexpr GridCost k32[4] = {{2.0, 1.56, 0.083, 0.050},
+int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled) {
+  static constexpr GridCost k32[5] = {{2.0, 1.56, 0.083, 0.050},
                                       {2.2, 1.31, 0.067, 0.050},
                                       {3.1, 0.32, 0.053, 0.014},
-                                      {2.3, 1.37, 0.100, 0.043}};
-  static constexpr GridCost k64[4] = {{2.0, 2.70, 0.124, 0.141},
+                                      {2.3, 1.37, 0.100, 0.043},
+                                      {2.1, 1.44, 0.124, 0.036}};
+  static constexpr GridCost k64[5] = {{2.0, 2.70, 0.124, 0.141},
                                       {1.6, 2.79, 0.113, 0.137},
                                       {2.5, 1.22, 0.089, 0.049},
-                                      {1.8, 2.45, 0.149, 0.149}};
-  static constexpr GridCost k128[4] = {{2.2, 4.38, 0.356, 0.258},
+                                      {1.8, 2.45, 0.149, 0.149},
+                                      {1.7, 2.37, 0.256, 0.154}};
+  static constexpr GridCost k128[5] = {{2.2, 4.38, 0.356, 0.258},
                                        {1.7, 4.61, 0.327, 0.274},
                                        {2.2, 2.37, 0.156, 0.072},
-                                       {2.2, 4.30, 0.394, 0.281}};
-  static constexpr GridCost k192[4] = {
-      {2.5, 7.53, 0.772, 0.479}, {}, {}, {2.7, 7.55, 0.867, 0.503}};
-  static constexpr GridCost kWide[4] = {{4.2, 13.14, 1.306, 0.618},
+                                       {2.2, 4.30, 0.394, 0.281},
+                                       {1.8, 3.86, 0.459, 0.281}};
+  static constexpr GridCost k192[5] = {{2.5, 7.53, 0.772, 0.479},
+                                       {},
+                                       {},
+                                       {2.7, 7.55, 0.867, 0.503},
+                                       {1.9, 7.05, 0.859, 0.575}};
+  static constexpr GridCost kWide[5] = {{4.2, 13.14, 1.306, 0.618},
                                         {2.9, 9.05, 0.660, 0.397},
                                         {1.6, 11.56, 0.601, 0.199},
-                                        {4.4, 6.95, 0.790, 0.435}};
+                                        {4.4, 6.95, 0.790, 0.435},
+                                        {2.1, 6.92, 0.809, 0.496}};
+  const int row = unscaled && variant == kElementwise ? 4 : variant;
   auto time = [&](const GridCost& c, int64_t bm, int64_t bn, int64_t together) {
     const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
     // A grid dimension holds less than 2^32 threads, which 32-wide tiles reach
@@ -492,16 +505,16 @@ int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant) {
       return HUGE_VAL;
     return grid_time(c, tiles, together, round_up(K, kKPad) / kSmallStep);
   };
-  const bool square = variant == kElementwise || variant == kHiOnly;
-  const double t32 = time(k32[variant], 32, 32, 512), t64 = time(k64[variant], 64, 64, 512);
-  const double t128 = time(k128[variant], 128, 128, 256);
+  const bool square = row == kElementwise || row == kHiOnly;
+  const double t32 = time(k32[row], 32, 32, 512), t64 = time(k64[row], 64, 64, 512);
+  const double t128 = time(k128[row], 128, 128, 256);
   // Machines differ by a few percent, and past one round the model is too kind to
   // the small tiles of the baseline.
   const double wide = (variant == kHiOnly ? 0.90 : 0.95) *
-                      time(kWide[variant], 256, square ? 256 : 128, 256);
+                      time(kWide[row], 256, square ? 256 : 128, 256);
   double best = std::min(std::min(t32, t64), std::min(t128, wide));
   if (variant == kElementwise || variant == kCrossFirst) {
-    const double t192 = time(k192[variant], 192, 192, 256);
+    const double t192 = time(k192[row], 192, 192, 256);
     if (t192 < best) return 192;
   }
   return best == wide ? 0 : best == t128 ? 128 : best == t64 ? 64 : 32;

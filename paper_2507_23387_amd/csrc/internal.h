@@ -182,9 +182,10 @@ hipError_t launch_unscale(const Planes& p, int64_t M, int64_t N, float* C, int64
 hipError_t launch_range_report(const Planes& p, bool empty, uint32_t* out, hipStream_t stream);
 
 // Tile side (32, 64, 128 or 192) of the kernel in gemm_small.hip that runs an
-// M x N x K problem in the order `variant`, or 0 for the 256-wide kernels.  A
-// tile's grid holds less than 2^32 threads.
-int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant);
+// M x N x K problem in the order `variant`, or 0 for the 256-wide kernels;
+// `unscaled`: the scale keeps the call on the unscaled body (scaled_kernel_ok).
+// A tile's grid holds less than 2^32 threads.
+int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled = false);
 
 // Threads per workgroup of that kernel.
 constexpr int small_tile_threads(int tile, int variant) {

@@ -164,13 +164,15 @@ void check_tile_picks(const char* file) {
   const struct {
     const char* name;
     int variant, column, tiles;  // columns: 256-wide, then 32, 64, 128 (and 192)
-  } orders[4] = {{"elementwise", sgc::kElementwise, 3, 5},
-                 {"termwise", sgc::kTermwise, 8, 4},
-                 {"baseline", sgc::kHiOnly, 12, 4},
-                 {"cross-first", sgc::kCrossFirst, 16, 5}};
+    bool unscaled;
+  } orders[5] = {{"elementwise", sgc::kElementwise, 3, 5, false},
+                 {"termwise", sgc::kTermwise, 8, 4, false},
+                 {"baseline", sgc::kHiOnly, 12, 4, false},
+                 {"cross-first", sgc::kCrossFirst, 16, 5, false},
+                 {"elementwise unscaled", sgc::kElementwise, 21, 5, true}};
   const int side[5] = {0, 32, 64, 128, 192};
-  double loss[4] = {0, 0, 0, 0};
-  int count = 0, slower[4] = {0, 0, 0, 0};
+  double loss[5] = {};
+  int count[5] = {}, slower[5] = {};
   std::FILE* f = std::fopen(file, "r");
   CHECK(f != nullptr);
   if (!f) return;
@@ -184,12 +186,14 @@ void check_tile_picks(const char* file) {
       else
         field.back() += *c;
     }
-    CHECK(field.size() == 21);
-    if (field.size() != 21) break;
-    ++count;
-    for (int o = 0; o < 4; ++o) {
+    CHECK(field.size() == 26);
+    if (field.size() != 26) break;
+    for (int o = 0; o < 5; ++o) {
+      if (field[orders[o].column].empty()) continue;
+      ++count[o];
       const int pick = sgc::small_gemm_tile(std::stoll(field[0]), std::stoll(field[1]),
-                                            std::stoll(field[2]), orders[o].variant);
+                                            std::stoll(field[2]), orders[o].variant,
+                                            orders[o].unscaled);
       double best = HUGE_VAL, picked = HUGE_VAL;
       for (int i = 0; i < orders[o].tiles; ++i) {
         const std::string& t = field[orders[o].column + i];
@@ -203,11 +207,11 @@ void check_tile_picks(const char* file) {
     }
   }
   std::fclose(f);
-  CHECK(count > 1000);
-  for (int o = 0; o < 4; ++o) {
+  for (int o = 0; o < 5; ++o) {
+    CHECK(count[o] > 1000);
     std::printf("%s: %d problems, %.4f slower than the fastest tile, %d slower than wide\n",
-                orders[o].name, count, loss[o] / count, slower[o]);
-    CHECK(loss[o] / count < 0.01 && slower[o] < 0.002 * count);
+                orders[o].name, count[o], loss[o] / count[o], slower[o]);
+    CHECK(loss[o] / count[o] < 0.01 && slower[o] < 0.002 * count[o]);
   }
 }
 
