@@ -163,15 +163,14 @@ bool splits_a_in_gemm(int64_t N, const float* A, int64_t lda, int64_t K, float s
 // 4096 x 4096 x 16384: 1197 against 1195; 8192 x 3072 x 4096: 534 against 526),
 // and when the range flag is set the plane path has its planes already, which
 // the fused kernel would first write at half a split pass's rate (4096 x 4096 x
-// 16384: 157 us against 94).  The kernels of gemm_small.hip read planes only: at
-// their sizes the split of A is a few microseconds (none of its own where B is
-// split by the same call), while splitting A in their registers made them
-// slower by 1.2-5 us at 300 x 200 x 1024 to 1024^3 and by 12 us at
-// 48 x 4096 x 4096 (18 to 30 us).
+// 16384: 157 us against 94).  The kernels of gemm_small.hip read planes only
+// (splitting A in their registers made them slower by 1.2-5 us at 300 x 200 x
+// 1024 to 1024^3 and by 12 us at 48 x 4096 x 4096, 18 to 30 us), so the pass over
+// A counts against them.
 bool gemm_reads_fp32_a(int64_t M, int64_t N, const float* A, int64_t lda, int64_t K, float scale,
                        int variant) {
   return splits_a_in_gemm(N, A, lda, K, scale, variant) && N <= kWideFusedMaxN &&
-         small_gemm_tile(M, N, K, variant, !scaled_kernel_ok(scale)) == 0;
+         small_gemm_tile(M, N, K, variant, !scaled_kernel_ok(scale), split_a_us(M, K)) == 0;
 }
 
 // GEMM from FP32 A and a workspace whose B planes are prepared: the 256-wide

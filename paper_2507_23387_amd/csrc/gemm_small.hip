@@ -469,7 +469,8 @@ double grid_time(const GridCost& c, int64_t tiles, int64_t together, int64_t kst
 // 192-wide tiles take the grids between 256 tiles of 128 and 256 of 256 (3072 x
 // 3072: 90 us, 118 on 128 and 115 on wide ones; 5760 x 5760 x 4096: 652 against
 // 712).
-int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled) {
+int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled,
+                    double split_us) {
   static constexpr GridCost k32[5] = {{2.0, 1.56, 0.083, 0.050},
                                       {2.2, 1.31, 0.067, 0.050},
                                       {3.1, 0.32, 0.053, 0.014},
@@ -510,14 +511,22 @@ int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled)
   const double t128 = time(k128[row], 128, 128, 256);
   // Machines differ by a few percent, and past one round the model is too kind to
   // the small tiles of the baseline.
-  const double wide = (variant == kHiOnly ? 0.90 : 0.95) *
-                      time(kWide[row], 256, square ? 256 : 128, 256);
-  double best = std::min(std::min(t32, t64), std::min(t128, wide));
-  if (variant == kElementwise || variant == kCrossFirst) {
-    const double t192 = time(k192[row], 192, 192, 256);
-    if (t192 < best) return 192;
-  }
-  return best == wide ? 0 : best == t128 ? 128 : best == t64 ? 64 : 32;
+  const double wide = time(kWide[row], 256, square ? 256 : 128, 256);
+  double limit = (variant == kHiOnly ? 0.90 : 0.95) * wide;
+  // Splitting A costs the 256-wide kernels 5 % (32768 x 256 x 1024 elementwise 76
+  // us; a pass over A and 128-wide tiles 97; 8192 x 1024 x 1024 the other way, 74
+  // and 64; termwise 16384 x 256 x 1024 42 and 47, 8192 x 256 x 4096 122 and 100).
+  if (split_us > 0) limit = std::min(limit, 1.05 * wide - split_us);
+  int tile = 0;
+  auto consider = [&](int side, double us) {
+    if (us < limit) limit = us, tile = side;
+  };
+  consider(32, time(k32[row], 32, 32, 512));
+  consider(64, time(k64[row], 64, 64, 512));
+  consider(128, time(k128[row], 128, 128, 256));
+  if (variant == kElementwise || variant == kCrossFirst)
+    consider(192, time(k192[row], 192, 192, 256));
+  return tile;
 }
 
 hipError_t launch_gemm_unscaled(const Planes& p, int64_t M, int64_t N, float* C, int64_t ldc,

@@ -155,6 +155,12 @@ hipError_t launch_split_rows(int64_t rows, int64_t cols, const float* X, int64_t
 // always zeroed.
 enum SplitPlanes { kSplitRows, kSplitPadded, kSplitHigh };
 
+// Microseconds that splitting A takes: 8 bytes an entry, read and written at 5.3
+// TB/s (a large device copy).
+inline double split_a_us(int64_t M, int64_t K) {
+  return 8.0 * static_cast<double>(M) * static_cast<double>(K) / 5.3e6;
+}
+
 // Enqueue, in one launch, the split of A (M x K row-major) into the tiled A
 // planes (A null: none) and of B (K x N row-major) into the tiled, transposed B
 // planes with the range flag (B null: none).  With opt.prescale row i of A
@@ -183,9 +189,12 @@ hipError_t launch_range_report(const Planes& p, bool empty, uint32_t* out, hipSt
 
 // Tile side (32, 64, 128 or 192) of the kernel in gemm_small.hip that runs an
 // M x N x K problem in the order `variant`, or 0 for the 256-wide kernels;
-// `unscaled`: the scale keeps the call on the unscaled body (scaled_kernel_ok).
-// A tile's grid holds less than 2^32 threads.
-int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled = false);
+// `unscaled`: the scale keeps the call on the unscaled body (scaled_kernel_ok);
+// `split_us`, if positive: the 256-wide kernel would split A itself, and a pass
+// that writes A's planes for the tiles takes this long (microseconds).  A tile's
+// grid holds less than 2^32 threads.
+int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled = false,
+                    double split_us = 0.0);
 
 // Threads per workgroup of that kernel.
 constexpr int small_tile_threads(int tile, int variant) {

@@ -156,6 +156,29 @@ void check_tile_rule() {
             }
 }
 
+// Where the 256-wide kernel splits A in registers, the tiles' pass over A counts:
+// a call of many rows and few columns keeps the 256-wide kernel, one whose pass
+// is short takes the tiles, and none takes tiles that it would not take on
+// planes.
+void check_split_in_rule() {
+  auto tile = [](int64_t M, int64_t N, int64_t K, int variant) {
+    return sgc::small_gemm_tile(M, N, K, variant, false, sgc::split_a_us(M, K));
+  };
+  CHECK(tile(32768, 256, 1024, sgc::kElementwise) == 0);
+  CHECK(tile(16384, 512, 2048, sgc::kElementwise) == 0);
+  CHECK(tile(16384, 256, 1024, sgc::kTermwise) == 0);
+  CHECK(tile(8192, 1024, 1024, sgc::kElementwise) != 0);
+  CHECK(tile(8192, 256, 4096, sgc::kElementwise) != 0);
+  CHECK(tile(8192, 256, 4096, sgc::kTermwise) != 0);
+  CHECK(tile(300, 200, 1024, sgc::kTermwise) != 0);
+  for (int variant : {sgc::kElementwise, sgc::kTermwise})
+    for (int64_t M = 1; M <= 1 << 20; M = M * 3 / 2 + 1)
+      for (int64_t N = 1; N <= 3072; N = N * 3 / 2 + 1)
+        for (int64_t K = 64; K <= 32768; K *= 2)
+          if (const int t = tile(M, N, K, variant))
+            CHECK(t == sgc::small_gemm_tile(M, N, K, variant));
+}
+
 // The rule's picks against measured times: per order the GEMM on the picked tile
 // is within 1 % of the fastest tile's on average, and more than 5 % slower than
 // on the 256-wide kernels (which have run these sizes too) on less than 0.2 % of
@@ -371,6 +394,7 @@ int main(int argc, char** argv) {
   const bool rule = argc > 2 && std::strcmp(argv[1], "rule") == 0;
   check_validation();
   check_tile_rule();
+  check_split_in_rule();
   if (rule) check_tile_picks(argv[2]);
   if (gpu) {
     int n = 0;
