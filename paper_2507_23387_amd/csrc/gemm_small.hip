@@ -507,8 +507,6 @@ int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled,
     return grid_time(c, tiles, together, round_up(K, kKPad) / kSmallStep);
   };
   const bool square = row == kElementwise || row == kHiOnly;
-  const double t32 = time(k32[row], 32, 32, 512), t64 = time(k64[row], 64, 64, 512);
-  const double t128 = time(k128[row], 128, 128, 256);
   // Machines differ by a few percent, and past one round the model is too kind to
   // the small tiles of the baseline.
   const double wide = time(kWide[row], 256, square ? 256 : 128, 256);
