@@ -43,7 +43,7 @@ THREE_GEMM_PEAK_TFLOPS = FP16_PEAK_TFLOPS / 3
 HBM_PEAK_GBS = 8000.0
 # The MFMA kernel that runs for each order: for the elementwise order the
 # 256 x 256 kernel that splits A in registers (where the library chooses it:
-# sgemm_cube_splits_a_in_gemm, N <= 3072) or the one that reads the A planes
+# sgemm_cube_splits_a_in_gemm) or the one that reads the A planes
 # (elsewhere, and with --unfused); either call also launches
 # the unscaled 256 x 128 kernel, which reads the range flag and returns at once
 # unless some |B_hi| s exceeds 65504, in which case it does the work.  For
@@ -379,8 +379,7 @@ def main():
     sh = stream.cuda_stream
 
     # A step enqueues what sgemm_cube_ws enqueues.  Where the library splits
-    # A inside the GEMM kernel (sgemm_cube_splits_a_in_gemm, on the 256-wide
-    # kernels and, elementwise, up to N = 3072) that is the split
+    # A inside the GEMM kernel (sgemm_cube_splits_a_in_gemm) that is the split
     # of B (sgemm_cube_prepare with A = NULL) and sgemm_cube_compute_a; else,
     # and with --unfused or --stages, the split of both operands
     # (sgemm_cube_prepare) and the GEMM on the tiled planes.
@@ -391,11 +390,13 @@ def main():
         print(f"--tile {args.tile}: the sweep covers the elementwise order and "
               f"{sgc.binding.TILE_CONFIGS}", file=sys.stderr)
         sys.exit(2)
+    # The one workload that runs on gemm_small.hip's tiles.
     small = max(M, N) <= 256 and not tile and not args.stages and not args.split_b_in_gemm
     fused = (not args.unfused and not args.stages and not args.prescale and not tile and
-             not small and (order != "elementwise" or N <= 3072) and
-             sgc.binding.sgemm_cube_splits_a_in_gemm(M, N, K, dA.data_ptr(), K, scale,
-                                                     order_code) == 1)
+             # With SPLIT_B_IN_GEMM: sgemm_cube_ex's condition for A (rows without padding).
+             (N <= 2048 and K % 64 == 0 if args.split_b_in_gemm else
+              sgc.binding.sgemm_cube_splits_a_in_gemm(M, N, K, dA.data_ptr(), K, scale,
+                                                      order_code) == 1))
     split_b = args.split_b_in_gemm
     if split_b and (order != "termwise" or args.prescale or args.stages or tile):
         print("--split-b-in-gemm: the termwise order only, without --prescale, --stages or "

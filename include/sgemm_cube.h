@@ -173,7 +173,8 @@ enum {
  *                B as well as A), the termwise GEMM kernel reads B as FP32 and
  *                splits it itself, each B tile once per tile row of C, instead
  *                of a split pass writing B's planes; A is split inside the
- *                kernel too where sgemm_cube_splits_a_in_gemm says so, so then
+ *                kernel too where N <= 2048, A is 16-byte aligned and lda is a
+ *                multiple of 4 and below 2^22 (else in a pass of its own), so then
  *                no plane reaches HBM.  The result is that of the termwise
  *                order without the option, bit for bit.  Requires
  *                accum_order = SGEMM_CUBE_TERMWISE, no PRESCALE, range_report
@@ -267,16 +268,14 @@ int sgemm_cube_compute_b(int64_t M, int64_t N, int64_t K, const float* B, int64_
  * sgemm_cube_compute_a with these arguments split A inside the GEMM kernel
  * instead of in a pass of its own, else 0 (also for arguments those calls
  * reject).  The in-kernel split repeats the split of each A tile for every
- * tile column of C, so it is chosen only where that costs less than the
- * pass over A: A 16-byte aligned, lda a multiple of 4 and below 2^22, K a
- * multiple of 64, and the elementwise order with N <= 4096 and
- * scale <= 2^15, or the termwise order with N <= 2048 (any scale).  Problems
- * whose 256-wide tiles would leave much of the GPU idle run on smaller tiles,
- * which read planes: there, and in the elementwise order above N = 3072, A is
- * split in the pass that splits B (compute_a: in a pass of its own) whatever
- * this returns, which measured as fast or faster.  Enqueues nothing and reads
- * no device memory (A is only looked at as an address).  Every choice gives
- * the same bits.
+ * tile column of C, and only the 256-wide kernels have it, so it is chosen
+ * where those kernels run and it costs less than the pass over A: A 16-byte
+ * aligned, lda a multiple of 4 and below 2^22, K a multiple of 64, and the
+ * elementwise order with N <= 3072 and scale <= 2^15, or the termwise order
+ * with N <= 2048 (any scale).  Problems that would leave much of the GPU idle
+ * on 256-wide tiles, the pass over A counted, run on smaller tiles, which read
+ * planes: 0.  Enqueues nothing and reads no device memory (A is only looked at
+ * as an address).  Every choice gives the same bits.
  */
 int sgemm_cube_splits_a_in_gemm(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                                 float scale, int accum_order);

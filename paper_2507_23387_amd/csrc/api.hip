@@ -139,47 +139,45 @@ RangeOpts range_opts(unsigned options, bool report, float scale) {
 // The in-kernel split of A redoes the split of an A tile once per tile
 // column of C, on the vector ALU between the matrix instructions, while the
 // split pass costs one read of A and one write of its planes through HBM.
-// Measured on MI355X: for the elementwise order (256-column tiles) the
-// in-kernel split is 13 % faster at M x N x K = 16384 x 1024 x 8192, 1 %
-// faster at 4096^3 and 4 % slower at 8192^3, so it is used up to N = 4096.
-// For termwise (128-column tiles, so twice the repeats per column of C): 10 %
-// faster at 16384 x 1024 x 8192, even at 4096^3 and 4 % slower at 4096 x 4096
-// x 16384, so it is used up to N = 2048.
-constexpr int64_t kFusedSplitMaxN = 4096;
+// Elementwise (256-column tiles): 13 % faster in the kernel at M x N x K = 16384
+// x 1024 x 8192; with both operands split by one launch the planes are as fast
+// at N = 4096 (4096^3: 312 us against 316, 4096 x 4096 x 16384: 1197 against
+// 1195; 8192 x 3072 x 4096: 534 against 526), and when the range flag is set the
+// plane path has its planes already, which the fused kernel would first write at
+// half a split pass's rate (4096 x 4096 x 16384: 157 us against 94), so it is
+// used up to N = 3072.  Termwise (128-column tiles, so twice the repeats per
+// column of C): 10 % faster at 16384 x 1024 x 8192, even at 4096^3 and 4 %
+// slower at 4096 x 4096 x 16384, so it is used up to N = 2048.
+constexpr int64_t kElementwiseFusedMaxN = 3072;
 constexpr int64_t kTermwiseFusedMaxN = 2048;
-constexpr int64_t kWideFusedMaxN = 3072;
 
-bool splits_a_in_gemm(int64_t N, const float* A, int64_t lda, int64_t K, float scale,
-                      int variant) {
-  const int64_t max_n = variant == kElementwise ? kFusedSplitMaxN
+// Whether the 256-wide kernels, where they run, split this A in registers.
+bool wide_kernel_splits_a(int64_t N, const float* A, int64_t lda, int64_t K, float scale,
+                          int variant) {
+  const int64_t max_n = variant == kElementwise ? kElementwiseFusedMaxN
                         : variant == kTermwise  ? kTermwiseFusedMaxN
                                                 : 0;
   return N <= max_n && fused_split_ok(A, lda, K, scale, variant);
 }
 
 // Whether the GEMM of this problem runs on FP32 A: the rule above, where the
-// 256-wide kernels run and, elementwise, N <= 3072: with both operands split by
-// one launch the planes are as fast at N = 4096 (4096^3: 312 us against 316,
-// 4096 x 4096 x 16384: 1197 against 1195; 8192 x 3072 x 4096: 534 against 526),
-// and when the range flag is set the plane path has its planes already, which
-// the fused kernel would first write at half a split pass's rate (4096 x 4096 x
-// 16384: 157 us against 94).  The kernels of gemm_small.hip read planes only
+// 256-wide kernels run.  The kernels of gemm_small.hip read planes only
 // (splitting A in their registers made them slower by 1.2-5 us at 300 x 200 x
 // 1024 to 1024^3 and by 12 us at 48 x 4096 x 4096, 18 to 30 us), so the pass over
 // A counts against them.
-bool gemm_reads_fp32_a(int64_t M, int64_t N, const float* A, int64_t lda, int64_t K, float scale,
-                       int variant) {
-  return splits_a_in_gemm(N, A, lda, K, scale, variant) && N <= kWideFusedMaxN &&
+bool splits_a_in_gemm(int64_t M, int64_t N, const float* A, int64_t lda, int64_t K, float scale,
+                      int variant) {
+  return wide_kernel_splits_a(N, A, lda, K, scale, variant) &&
          small_gemm_tile(M, N, K, variant, !scaled_kernel_ok(scale), split_a_us(M, K)) == 0;
 }
 
 // GEMM from FP32 A and a workspace whose B planes are prepared: the 256-wide
-// kernel splits A in registers when gemm_reads_fp32_a says so, else A is split
+// kernel splits A in registers when splits_a_in_gemm says so, else A is split
 // into the workspace first and the GEMM runs on the planes.
 hipError_t compute_from_a(const Planes& p, int64_t M, int64_t N, int64_t K, const float* A,
                           int64_t lda, float* C, int64_t ldc, float scale, int variant,
                           hipStream_t stream) {
-  if (gemm_reads_fp32_a(M, N, A, lda, K, scale, variant))
+  if (splits_a_in_gemm(M, N, A, lda, K, scale, variant))
     return launch_gemm_fused_a(p, M, N, K, A, lda, C, ldc, scale, variant, stream);
   const hipError_t e = launch_split(p, M, N, K, A, lda, nullptr, 0, scale, RangeOpts{},
                                     next_stamp(), 0, kSplitRows, stream);
@@ -203,8 +201,8 @@ int run(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const floa
   const Planes p = plan_planes(M, N, K, ws, opt.prescale);
   if (split_b_in_gemm) {
     // Termwise with B split inside the GEMM kernel (validated by the caller);
-    // A too where the library splits it there, else by its own pass.
-    const bool fused_a = splits_a_in_gemm(N, A, lda, K, scale, variant);
+    // A too where that kernel splits it, else by its own pass.
+    const bool fused_a = wide_kernel_splits_a(N, A, lda, K, scale, variant);
     if (!fused_a &&
         launch_split(p, M, N, K, A, lda, nullptr, 0, scale, opt, next_stamp(), 0, kSplitRows,
                      stream) != hipSuccess)
@@ -214,7 +212,7 @@ int run(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const floa
                ? SGEMM_CUBE_OK
                : SGEMM_CUBE_ERR_HIP;
   }
-  if (!opt.prescale && !opt.report && gemm_reads_fp32_a(M, N, A, lda, K, scale, variant)) {
+  if (!opt.prescale && !opt.report && splits_a_in_gemm(M, N, A, lda, K, scale, variant)) {
     // B is split into the workspace, A inside the GEMM kernel.
     if (launch_split(p, M, N, K, nullptr, 0, B, ldb, scale, opt, 0, next_stamp(), kSplitRows,
                      stream) != hipSuccess)
@@ -653,7 +651,7 @@ int sgemm_cube_splits_a_in_gemm(int64_t M, int64_t N, int64_t K, const float* A,
     return 0;
   if (accum_order < SGEMM_CUBE_ELEMENTWISE || accum_order > SGEMM_CUBE_ELEMENTWISE_CROSS_FIRST)
     return 0;
-  return sgc::splits_a_in_gemm(N, A, lda, K, scale, sgc::variant_of(accum_order)) ? 1 : 0;
+  return sgc::splits_a_in_gemm(M, N, A, lda, K, scale, sgc::variant_of(accum_order)) ? 1 : 0;
 }
 
 int sgemm_cube_compute_stages(int64_t M, int64_t N, int64_t K, float* C, int64_t ldc,

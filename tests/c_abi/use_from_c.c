@@ -35,9 +35,9 @@ int main(void) {
         SGEMM_CUBE_ERR_INVALID_VALUE);
   CHECK(sgemm_cube(4, 4, 4, A, 3, B, 4, C, 4, 2048.0f, SGEMM_CUBE_ELEMENTWISE, NULL) ==
         SGEMM_CUBE_ERR_INVALID_VALUE);
-  CHECK(sgemm_cube_splits_a_in_gemm(1024, 1024, 1024, A, 1024, 2048.0f,
+  CHECK(sgemm_cube_splits_a_in_gemm(16384, 1024, 1024, A, 1024, 2048.0f,
                                     SGEMM_CUBE_ELEMENTWISE) == 1);
-  CHECK(sgemm_cube_splits_a_in_gemm(1024, 8192, 1024, A, 1024, 2048.0f,
+  CHECK(sgemm_cube_splits_a_in_gemm(16384, 8192, 1024, A, 1024, 2048.0f,
                                     SGEMM_CUBE_ELEMENTWISE) == 0);
   printf("%d\n", bad);
   return bad;

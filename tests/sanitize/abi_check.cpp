@@ -125,9 +125,10 @@ void check_validation() {
   CHECK(sgemm_cube_hgemm(4, 4, 4, A, 3, B, 4, C, 4, nullptr) == INV);
   CHECK(sgemm_cube_hgemm(0, 4, 4, A, 4, B, 4, C, 4, nullptr) == 0);
   // Queries.
-  CHECK(sgemm_cube_splits_a_in_gemm(512, 4096, 1024, A, 1024, 2048.f, 0) == 1);
-  CHECK(sgemm_cube_splits_a_in_gemm(512, 4097, 1024, A, 1024, 2048.f, 0) == 0);
-  CHECK(sgemm_cube_splits_a_in_gemm(512, 4096, 1024, fake<float>(4), 1024, 2048.f, 0) == 0);
+  CHECK(sgemm_cube_splits_a_in_gemm(16384, 3072, 1024, A, 1024, 2048.f, 0) == 1);
+  CHECK(sgemm_cube_splits_a_in_gemm(16384, 3073, 1024, A, 1024, 2048.f, 0) == 0);
+  CHECK(sgemm_cube_splits_a_in_gemm(512, 512, 1024, A, 1024, 2048.f, 0) == 0);
+  CHECK(sgemm_cube_splits_a_in_gemm(16384, 3072, 1024, fake<float>(4), 1024, 2048.f, 0) == 0);
   CHECK(sgemm_cube_block_k() == 32);
   for (int st = -1; st <= 5; ++st) CHECK(sgemm_cube_status_string(st) != nullptr);
   CHECK(std::string(sgemm_cube_status_string(SGEMM_CUBE_ERR_ALLOC)) == "SGEMM_CUBE_ERR_ALLOC");

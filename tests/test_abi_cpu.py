@@ -279,17 +279,21 @@ def test_compute_a_validation(lib):
 
 def test_splits_a_in_gemm_rule(lib):
     """The in-kernel split of A is chosen for the elementwise order with
-    N <= 4096, scale <= 2^15, 16-byte aligned A, lda % 4 == 0 and below 2^22,
+    N <= 3072, scale <= 2^15, 16-byte aligned A, lda % 4 == 0 and below 2^22,
     and K % 64 == 0, and for termwise with the same layout and N <= 2048 at any
-    valid scale; everything else, and invalid arguments, gets 0.  The query only
-    looks at A's address."""
-    q = lambda M=512, N=4096, K=1024, A=FAKE, lda=1024, scale=2048.0, order=0: \
+    valid scale, where the 256-wide kernels run (so not for calls that the
+    smaller tiles take); everything else, and invalid arguments, gets 0.  The
+    query only looks at A's address."""
+    q = lambda M=16384, N=3072, K=1024, A=FAKE, lda=1024, scale=2048.0, order=0: \
         lib.sgemm_cube_splits_a_in_gemm(M, N, K, A, lda, scale, order)
     assert q() == 1
-    assert q(N=1) == 1 and q(M=1) == 1 and q(K=64) == 1
+    assert q(M=32768, N=256) == 1 and q(N=256, order=1) == 1
     assert q(scale=32768.0) == 1 and q(scale=1.0) == 1
     assert q(lda=1028) == 1
-    assert q(N=4097) == 0                      # many tile columns: split pass
+    assert q(N=3073) == 0 and q(N=4096) == 0    # many tile columns: split pass
+    # Smaller tiles, which read planes.
+    assert q(M=512) == 0 and q(M=1) == 0 and q(N=1) == 0
+    assert q(M=300, N=200) == 0 and q(M=300, N=200, order=1) == 0
     assert q(order=2) == 0                      # cross-terms-first: never
     assert q(order=1) == 0                      # termwise: N <= 2048 only
     assert q(order=1, N=2048) == 1              # the 256 x 128 kernel

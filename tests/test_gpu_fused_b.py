@@ -53,8 +53,9 @@ def _mixed_operands(M, N, K, seed):
 
 def _with_and_without(A, B, scale=2048.0, pads=(0, 0, 0), a_offset=0):
     """(C with the option, C without), each written into a NaN-filled C with
-    ldc = N + pads[2]; the columns past N and the rows past M stay NaN.  The
-    third route, sgemm_cube_prepare(A, B = NULL) + sgemm_cube_compute_b, is
+    ldc = N + pads[2]; the columns past N and the rows past M stay NaN.  With the
+    option A's planes are written exactly where _fused_a says no.  The third
+    route, sgemm_cube_prepare(A, B = NULL) + sgemm_cube_compute_b, is
     checked against the first bit for bit here."""
     import torch
 
@@ -70,7 +71,7 @@ def _with_and_without(A, B, scale=2048.0, pads=(0, 0, 0), a_offset=0):
     out = []
     for options in (opt, 0):
         nbytes = binding.sgemm_cube_ex_workspace_size(M, N, K, binding.TERMWISE, options)
-        ws = torch.empty((max(nbytes, 1),), dtype=torch.uint8, device="cuda")
+        ws = torch.full((max(nbytes, 1),), 0xAB, dtype=torch.uint8, device="cuda")
         cbuf, dC = padded(np.full((M, N), np.nan, np.float32), ldc)
         cbuf.fill_(float("nan"))
         st = binding.sgemm_cube_ex(M, N, K, dA.data_ptr(), lda, dB.data_ptr(), ldb,
@@ -78,6 +79,8 @@ def _with_and_without(A, B, scale=2048.0, pads=(0, 0, 0), a_offset=0):
                                    ws.data_ptr(), nbytes, None, stream)
         assert st == 0, binding.sgemm_cube_status_string(st)
         torch.cuda.synchronize()
+        if options:  # A's planes come first, after a header of 256 bytes
+            assert bool((ws[256:256 + 1024] == 0xAB).all()) == _fused_a(M, N, K, a_offset, lda)
         full = cbuf.cpu().numpy()
         assert np.isnan(full[:M * ldc].reshape(M, ldc)[:, N:]).all()
         assert np.isnan(full[M * ldc:]).all()
@@ -103,17 +106,10 @@ def _fused_a(M, N, K, a_offset=0, lda=None):
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_split_b_in_gemm_gives_the_bits_of_the_planes_path(gpu, shape):
-    from paper_2507_23387_amd import binding
-
     M, N, K = shape
     A, B = _mixed_operands(M, N, K, 5 * M + N + 3 * K)
     log(f"split of B in the GEMM vs planes {M}x{N}x{K} "
         f"(A {'in the GEMM' if _fused_a(M, N, K) else 'split pass'})")
-    import torch
-
-    dA = torch.from_numpy(A).cuda()
-    assert binding.sgemm_cube_splits_a_in_gemm(M, N, K, dA.data_ptr(), K, 2048.0,
-                                               binding.TERMWISE) == int(_fused_a(M, N, K))
     Cf, Cp = _with_and_without(A, B)
     _same_bits(Cf, Cp)
     Co = oracle.sgemm(A, B, 2048.0, "termwise", kb=_kb())
