@@ -406,8 +406,9 @@ int run_allocating(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
 // address is looked up once per device with hipGetSymbolAddress, with that
 // device current, and only that address is passed to kernels.  The array's
 // header words are stamped by every split (a fresh stamp per call), so nothing
-// in it has to start at zero; the planes are fully rewritten by the splits of
-// each call, padding included.
+// in it has to start at zero; the splits of each call rewrite the planes' own
+// rows and zero the padding of K.  The padding rows of M and N keep any bits:
+// they feed only entries of C that are never stored.
 static __device__ __align__(256) unsigned char scratch[SGEMM_CUBE_NOALLOC_WORKSPACE_BYTES];
 std::mutex g_scratch_mu;
 void* g_scratch[kMaxDevices] = {};
