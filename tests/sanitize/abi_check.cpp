@@ -239,6 +239,40 @@ void check_tile_picks(const char* file) {
   }
 }
 
+// The picks for the shapes of the GPU tests (tests/golden/tile_picks.txt), and
+// that the problem those tests compare them with runs on the 256-wide kernels.
+void check_golden_picks(const char* file) {
+  std::FILE* f = std::fopen(file, "r");
+  CHECK(f != nullptr);
+  if (!f) return;
+  static const struct {
+    int variant;
+    bool unscaled;
+  } columns[5] = {{sgc::kElementwise, false}, {sgc::kElementwise, true}, {sgc::kTermwise, false},
+                  {sgc::kHiOnly, false}, {sgc::kCrossFirst, false}};
+  int lines = 0;
+  char line[512];
+  while (std::fgets(line, sizeof line, f)) {
+    long long M, N, K;
+    int want[5];
+    if (std::sscanf(line, "%lld %lld %lld %d %d %d %d %d", &M, &N, &K, &want[0], &want[1], &want[2],
+                    &want[3], &want[4]) != 8)
+      continue;  // comment
+    ++lines;
+    for (int o = 0; o < 5; ++o) {
+      const int got = sgc::small_gemm_tile(M, N, K, columns[o].variant, columns[o].unscaled);
+      if (got != want[o]) {
+        std::fprintf(stderr, "order %d: %lldx%lldx%lld picks %d, not %d\n", o, M, N, K, got,
+                     want[o]);
+        ++failures;
+      }
+      CHECK(sgc::small_gemm_tile(4070, 4090, K, columns[o].variant, columns[o].unscaled) == 0);
+    }
+  }
+  std::fclose(f);
+  CHECK(lines >= 8);
+}
+
 // ---------------------------------------------------------------- GPU part
 
 uint64_t g_lcg = 0x9e3779b97f4a7c15ULL;
@@ -393,10 +427,12 @@ void check_gpu(hipStream_t s) {
 int main(int argc, char** argv) {
   const bool gpu = argc > 1 && std::strcmp(argv[1], "gpu") == 0;
   const bool rule = argc > 2 && std::strcmp(argv[1], "rule") == 0;
+  const bool picks = argc > 2 && std::strcmp(argv[1], "picks") == 0;
   check_validation();
   check_tile_rule();
   check_split_in_rule();
   if (rule) check_tile_picks(argv[2]);
+  if (picks) check_golden_picks(argv[2]);
   if (gpu) {
     int n = 0;
     CHECK(hipGetDeviceCount(&n) == hipSuccess && n > 0);
@@ -413,6 +449,6 @@ int main(int argc, char** argv) {
     std::fprintf(stderr, "%d checks failed\n", failures);
     return 1;
   }
-  std::printf("abi_check %s: all checks passed\n", gpu ? "gpu" : rule ? "rule" : "cpu");
+  std::printf("abi_check %s: all checks passed\n", gpu ? "gpu" : rule ? "rule" : picks ? "picks" : "cpu");
   return 0;
 }

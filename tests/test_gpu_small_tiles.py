@@ -1,26 +1,28 @@
 """The 32, 64, 128 and 192-wide tile kernels that the library picks for problems
-whose 256-wide tiles leave compute units idle, at tile edges and remainders.
-
-Elementwise: bit for bit the 256 x 256 sweep kernel on the same planes (scaled
-body, range fallback, s > 2^15).  Termwise: bit for bit the 256 x 128 kernel
-that splits B itself.  Cross-terms-first (both bodies) and the FP16 baseline:
-the oracle, within the bar 2 K 2^-24 |A||B|."""
+whose 256-wide tiles leave compute units idle, at tile edges and remainders: in
+every order (range fallback, s > 2^15, pre-scaling and the report too) bit for
+bit the rows and columns of a larger problem that runs on the 256-wide kernels,
+whose sampled rows meet the oracle within the bar 2 K 2^-24 |A||B|.  Elementwise
+also bit for bit the 256 x 256 sweep kernel on the same planes, termwise the
+256 x 128 kernel that splits B itself."""
 import numpy as np
 import pytest
 
 import oracle
 import workloads
 from tests.gpu_util import gemm, hgemm, log, to_dev
-from tests.helpers import abs_ab, assert_parity, band_rows
+from tests.helpers import abs_ab, assert_parity, band_rows, read_table
 
 pytestmark = pytest.mark.gpu
 
 # (M, N, K): one 32-wide tile with remainders, grids of 32, 64, 128 and 192-wide
 # tiles that end inside a tile (the last past the planes' padded rows: 2600 lies
-# in 14 tiles of 192, 2688 rows, and pads to 2816; 2740 in 15, 2880); K from one
-# step of 64.
-SHAPES = [(31, 36, 64), (257, 260, 192), (512, 512, 64), (700, 1020, 192), (1500, 1660, 704),
-          (2777, 3000, 320)]
+# in 14 tiles of 192, 2688 rows, and pads to 2816; 2740 in 15, 2880), and the
+# 256-wide kernels; K from one step of 64.  The table names each order's tile.
+SHAPES = [tuple(int(v) for v in row[:3]) for row in read_table("tile_picks.txt")]
+# A problem of these rows and columns runs on the 256-wide kernels in every order
+# at every K of SHAPES.
+WIDE = (4070, 4090)
 
 
 @pytest.mark.parametrize("overflow,scale", [(False, 2048.0), (True, 2048.0), (False, 65536.0)],
@@ -68,6 +70,94 @@ def test_termwise_gives_the_wide_kernels_bits(gpu, shape):
     wide = binding.matmul_ex(dA, dB, order="termwise", split_b_in_gemm=True)
     torch.cuda.synchronize()
     assert torch.equal(got.view(torch.int32), wide.view(torch.int32))
+
+
+KINDS = {  # order, scale, B overflows, pre-scaling
+    "elementwise": ("elementwise", 2048.0, False, False),
+    "elementwise_range": ("elementwise", 2048.0, True, False),
+    "elementwise_large_scale": ("elementwise", 65536.0, False, False),
+    "termwise": ("termwise", 4096.0, False, False),
+    "cross": ("elementwise_cross_first", 2048.0, False, False),
+    "cross_range": ("elementwise_cross_first", 2048.0, True, False),
+    "cross_large_scale": ("elementwise_cross_first", 65536.0, False, False),
+    "hgemm": ("hi_only", 2048.0, False, False),
+    "prescale_elementwise": ("elementwise", 2048.0, False, True),
+    "prescale_termwise": ("termwise", 2048.0, False, True),
+    "prescale_cross": ("elementwise_cross_first", 2048.0, False, True),
+}
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_rows_and_columns_of_a_wide_problem(gpu, shape, kind):
+    """An entry of C depends on its row of A and its column of B alone, so C of
+    (A, B) is that part of the product of A's rows and B's columns repeated to
+    4070 x 4090, which runs on the 256-wide kernels."""
+    import torch
+
+    from paper_2507_23387_amd import binding
+
+    M, N, K = shape
+    order, scale, overflow, prescale = KINDS[kind]
+    A, B = workloads.make_operands(M, N, K, M + K, "normal")
+    if overflow:
+        B[K - 1, N - 1] = np.float32(40.0)
+    if prescale:
+        rng = np.random.default_rng(M)
+        exp = rng.integers(-28, 20, (M, 1))
+        A = np.ldexp(A, exp).astype(np.float32)
+        B = np.ldexp(B, rng.integers(-28, 20, (1, N))).astype(np.float32)
+        # An FP16-subnormal hi after the scaling to [2^14, 2^15).
+        A[M // 2, K // 2] = np.ldexp(1.0, exp[M // 2, 0] - 32)
+    log(f"small tiles {kind} {M}x{N}x{K} and wide")
+    dA, dB = to_dev(A), to_dev(B)
+    wM, wN = max(M, WIDE[0]), max(N, WIDE[1])
+    wA = dA[torch.arange(wM, device="cuda") % M].contiguous()
+    wB = dB[:, torch.arange(wN, device="cuda") % N].contiguous()
+
+    def call(a, b):
+        if order == "hi_only":
+            return binding.hgemm(a, b), None
+        if prescale:
+            return binding.matmul_ex(a, b, scale=scale, order=order, prescale=True, report=True)
+        return binding.matmul(a, b, scale=scale, order=order), None
+
+    C, bits = call(dA, dB)
+    W, wbits = call(wA, wB)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(C).all())
+    assert torch.equal(C.view(torch.int32), W[:M, :N].contiguous().view(torch.int32))
+    rows = band_rows(wM, K)
+    Ah, Wh = A[rows % M], W.cpu().numpy()[rows]
+    Bw = wB.cpu().numpy()
+    if prescale:
+        assert int(bits.item()) == int(wbits.item()) == binding.RANGE_HI_SUBNORMAL
+        # A line's power of two follows from the line, so sampled rows suffice.
+        want = oracle.sgemm_prescaled(Ah, Bw, scale, order, kb=32)
+    else:
+        want = oracle.sgemm(Ah, Bw, scale, order, kb=32)
+    assert_parity(Wh, want, K, abs_ab(Ah, Bw), f"wide {kind} {shape}")
+
+
+@pytest.mark.parametrize("bit", ["clean", "all"])
+def test_report_of_a_wide_problem(gpu, bit):
+    """The report without pre-scaling after a 256-wide GEMM: none and all of the
+    range classes."""
+    import torch
+
+    from paper_2507_23387_amd import binding
+
+    M, N, K = WIDE + (64,)
+    A, B = workloads.make_operands(M, N, K, 5, "uniform_pm1")
+    A, B = np.sign(A) * (np.abs(A) + 1), np.sign(B) * (np.abs(B) + 1)  # no subnormal hi
+    if bit == "all":
+        A[M - 1, K - 1], A[7, 3] = 70000.0, 2.0**-20
+        B[K - 1, N - 1], B[3, 5] = np.nan, 32784.0
+    log(f"report of a wide problem: {bit}")
+    C, bits = binding.matmul_ex(to_dev(A), to_dev(B), scale=4096.0, order="termwise", report=True)
+    torch.cuda.synchronize()
+    want = oracle.range_classes(A, 4096.0) | oracle.range_classes(B, 4096.0)
+    assert int(bits.item()) == want == (15 if bit == "all" else 0)
 
 
 @pytest.mark.parametrize("kind", ["cross", "cross_range", "hgemm"])

@@ -51,3 +51,6 @@ def test_abi_host_code_under_asan_ubsan(tmp_path):
     # The GEMM's tile rule against the measured times it was fitted to.
     out = _run([exe, "rule", os.path.join(ROOT, "profiles", "tile_rule_grids.csv")], timeout=120)
     assert "abi_check rule: all checks passed" in out
+    # And its picks for the shapes of the GPU tests.
+    out = _run([exe, "picks", os.path.join(ROOT, "tests", "golden", "tile_picks.txt")], timeout=120)
+    assert "abi_check picks: all checks passed" in out
