@@ -74,6 +74,36 @@ def test_prescaling_is_exact_on_normal_two_word_inputs(gpu, order):
     assert np.array_equal(plain.view(np.uint32), pre.view(np.uint32))
 
 
+@pytest.mark.parametrize("K", [1, 3, 31, 255, 257, 2047, 4096, 4100])
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 31, 34, 63])
+def test_prescaled_maxima_at_the_edges(gpu, N, K):
+    """The maxima of rows and columns that end inside a 16-byte piece or a
+    chunk: each line's largest entry is its first or last, neighbouring lines lie
+    48 binades apart, and a NaN and an infinity are passed over."""
+    import torch
+
+    from paper_2507_23387_amd import binding
+    from tests.gpu_util import padded
+
+    M = 5
+    rng = np.random.default_rng(N + 100 * K)
+    A, B = rng.uniform(0.25, 0.5, (M, K)), rng.uniform(0.25, 0.5, (K, N))
+    A[np.arange(M), np.where(np.arange(M) % 3, K - 1, 0)] = 1.0
+    B[np.where(np.arange(N) % 3, 0, K - 1), np.arange(N)] = 1.0
+    A = np.ldexp(A, np.where(np.arange(M) % 2, -28, 20)[:, None]).astype(np.float32)
+    B = np.ldexp(B, np.where(np.arange(N) % 2, 20, -28)[None, :]).astype(np.float32)
+    if K > 3:
+        A[1, K // 2] = np.nan
+        B[K // 3, N // 2] = np.inf
+    log(f"ex prescale maxima {M}x{N}x{K}")
+    _, vA = padded(A, K + 3, offset=1)
+    _, vB = padded(B, N + 1, offset=3)
+    C = binding.matmul_ex(vA[:, :K], vB[:, :N], order="termwise", prescale=True)
+    torch.cuda.synchronize()
+    want = oracle.sgemm_prescaled(A, B, 2048.0, "termwise", kb=_kb())
+    assert_parity(C.cpu().numpy(), want, K, abs_ab(A, B), f"prescale maxima {N} {K}")
+
+
 def test_prescaling_restores_main_bound_for_deep_subnormal_hi(gpu):
     """|a| ~ 2^-22: hi is FP16-subnormal with 2 significant bits (Sec. 4.2,
     after Rule 1); unscaled the termwise result breaks Eq. main_bound,
