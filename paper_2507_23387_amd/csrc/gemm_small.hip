@@ -515,8 +515,13 @@ int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled,
   // us; a pass over A and 128-wide tiles 97; 8192 x 1024 x 1024 the other way, 74
   // and 64; termwise 16384 x 256 x 1024 42 and 47, 8192 x 256 x 4096 122 and 100).
   if (split_us > 0) limit = std::min(limit, 1.05 * wide - split_us);
+  // Planes of A that the 256 MiB last-level cache cannot hold come back from HBM,
+  // at the rate they went (27840 x 5 x 8832 elementwise: 496 us on the 256-wide
+  // kernel, 532 on 32-wide tiles).
+  const double read_us = 4.0 * M * K > 256.0 * (1 << 20) ? 0.5 * split_us : 0.0;
   int tile = 0;
   auto consider = [&](int side, double us) {
+    us = std::max(us, read_us);
     if (us < limit) limit = us, tile = side;
   };
   consider(32, time(k32[row], 32, 32, 512));

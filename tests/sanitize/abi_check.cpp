@@ -168,6 +168,7 @@ void check_split_in_rule() {
   CHECK(tile(32768, 256, 1024, sgc::kElementwise) == 0);
   CHECK(tile(16384, 512, 2048, sgc::kElementwise) == 0);
   CHECK(tile(16384, 256, 1024, sgc::kTermwise) == 0);
+  CHECK(tile(27840, 5, 8832, sgc::kElementwise) == 0);  // planes past the last-level cache
   CHECK(tile(8192, 1024, 1024, sgc::kElementwise) != 0);
   CHECK(tile(8192, 256, 4096, sgc::kElementwise) != 0);
   CHECK(tile(8192, 256, 4096, sgc::kTermwise) != 0);
