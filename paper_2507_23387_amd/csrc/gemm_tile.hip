@@ -245,7 +245,7 @@ hipError_t launch_gemm_tile(const Planes& p, int64_t M, int64_t N, float* C, int
                             float scale, int tile_m, int tile_n, int block_k, int waves,
                             hipStream_t stream) {
   if (!tile_config_ok(tile_m, tile_n, block_k, waves)) return hipErrorInvalidValue;
-  if (!scaled_kernel_ok(scale)) 
+  if (!scaled_kernel_ok(scale))
     return launch_gemm_unscaled(p, M, N, C, ldc, scale, kElementwise, true, stream);
   hipError_t e = hipSuccess;
   if (waves == 8)
