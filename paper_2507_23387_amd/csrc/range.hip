@@ -52,10 +52,13 @@ __device__ __forceinline__ void absmax_rows(int64_t block, int64_t M, int64_t K,
   if (i >= M) return;
   const float* const row = A + i * lda;
   float m = 0.0f;
+  // 2048 elements from k0, or those there are (`whole` false).
   auto chunk = [&](int64_t k0, auto whole) {
+    const int pieces = whole.value ? kAbsUnroll : static_cast<int>((K - k0 + 255) / 256);
     floatx4_u v[kAbsUnroll];
 #pragma unroll
     for (int u = 0; u < kAbsUnroll; ++u) {
+      if (u >= pieces) break;
       const int64_t k = k0 + u * 256 + lane * 4;
       if constexpr (whole.value)
         v[u] = *reinterpret_cast<const floatx4_u*>(row + k);
@@ -63,9 +66,11 @@ __device__ __forceinline__ void absmax_rows(int64_t block, int64_t M, int64_t K,
         v[u] = k < K ? load_quad(row, quad_start(k, K), K) : floatx4_u{0.0f, 0.0f, 0.0f, 0.0f};
     }
 #pragma unroll
-    for (int u = 0; u < kAbsUnroll; ++u)
+    for (int u = 0; u < kAbsUnroll; ++u) {
+      if (u >= pieces) break;
 #pragma unroll
       for (int e = 0; e < 4; ++e) m = max_finite(m, v[u][e]);
+    }
   };
   int64_t k0 = 0;
   for (; k0 + kAbsUnroll * 256 <= K; k0 += kAbsUnroll * 256) chunk(k0, std::true_type{});
@@ -92,24 +97,31 @@ __device__ __forceinline__ void absmax_cols(int64_t strip, int64_t k0, int64_t k
   float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   if (j < N) {
     const int64_t first = quad_start(j, N);
+    // 256 rows from kb, or those there are (`whole` false).
     auto chunk = [&](int64_t kb, auto whole) {
+      const int pieces =
+          whole.value ? kAbsUnroll : static_cast<int>(min<int64_t>(kAbsUnroll, (k1 - kb + 31) / 32));
       floatx4_u v[kAbsUnroll];
 #pragma unroll
       for (int u = 0; u < kAbsUnroll; ++u) {
+        if (u >= pieces) break;
         const int64_t k = kb + u * 32 + (t >> 3);
-        if (whole.value || k < k1)
-          v[u] = load_quad(B + k * ldb, first, N);
+        if constexpr (whole.value)
+          v[u] = *reinterpret_cast<const floatx4_u*>(B + k * ldb + first);
         else
-          v[u] = floatx4_u{0.0f, 0.0f, 0.0f, 0.0f};
+          v[u] = k < k1 ? load_quad(B + k * ldb, first, N) : floatx4_u{0.0f, 0.0f, 0.0f, 0.0f};
       }
 #pragma unroll
-      for (int u = 0; u < kAbsUnroll; ++u)
+      for (int u = 0; u < kAbsUnroll; ++u) {
+        if (u >= pieces) break;
 #pragma unroll
         for (int e = 0; e < 4; ++e) m[e] = max_finite(m[e], v[u][e]);
+      }
     };
     int64_t kb = k0;
-    for (; kb + kAbsUnroll * 32 <= k1; kb += kAbsUnroll * 32) chunk(kb, std::true_type{});
-    if (kb < k1) chunk(kb, std::false_type{});
+    if (N >= 4)
+      for (; kb + kAbsUnroll * 32 <= k1; kb += kAbsUnroll * 32) chunk(kb, std::true_type{});
+    for (; kb < k1; kb += kAbsUnroll * 32) chunk(kb, std::false_type{});
     // Column j + e is element j - first + e of that quad.
     const int shift = static_cast<int>(j - first);
 #pragma unroll
@@ -137,7 +149,7 @@ __device__ __forceinline__ void absmax_cols(int64_t strip, int64_t k0, int64_t k
 }
 
 // Row maxima of A (the first row_blocks workgroups) and column maxima of B.  A
-// column's workgroup walks all of K: 1024^3 6 us in this one launch, against 4 +
+// column's workgroup walks all of K: 1024^3 5 us in this one launch, against 4 +
 // 18.5 us as two, with scalar loads and 64 rows of a column per workgroup.
 __global__ __launch_bounds__(256) void absmax_kernel(uint32_t row_blocks, int64_t M, int64_t N,
                                                      int64_t K, const float* __restrict__ A,
@@ -206,7 +218,7 @@ hipError_t launch_absmax(const Planes& p, int64_t M, int64_t N, int64_t K, const
                          int64_t lda, const float* B, int64_t ldb, hipStream_t stream) {
   const int64_t row_blocks = (M + kAbsRows - 1) / kAbsRows;
   const int64_t strips = (N + kAbsCols - 1) / kAbsCols;
-  // One launch while a column's workgroup walks at most 4096 rows (about 15
+  // One launch while a column's workgroup walks at most 4096 rows (about 12
   // us) and the blocks fit a grid; past that the columns are cut along K, into
   // maxima that a launch before clears.
   if (K <= 4096 && row_blocks + strips <= (1 << 23)) {
