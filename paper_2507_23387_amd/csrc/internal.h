@@ -43,6 +43,15 @@ __host__ __device__ inline int64_t tiled_index(int64_t row, int64_t k, int64_t K
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
+// Workgroup `index` of a grid of nwg runs on XCD index % 8 (each with its own
+// L2): the position in the tile order that gives every XCD consecutive tiles,
+// the first nwg % 8 XCDs one more than the others.  tile_of (gemm_common.h) does
+// the same for grids of a multiple of 8.
+__host__ __device__ inline int xcd_order(int index, int nwg) {
+  const int x = index & 7, rest = nwg & 7;
+  return x * (nwg >> 3) + (x < rest ? x : rest) + (index >> 3);
+}
+
 // The two-component split of one value (Sec. 3.3, Eq. recover_eqn):
 // hi = fl16(a), r = a - hi (exact in FP32), lo = fl16(r * s), RN-even with
 // gradual underflow.  Shared by the split kernels and the GEMM that splits A

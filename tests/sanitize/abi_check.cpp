@@ -157,6 +157,24 @@ void check_tile_rule() {
             }
 }
 
+// The order of a grid's tiles reaches every tile once and gives each XCD (every
+// eighth workgroup) consecutive ones, also where the grid is no multiple of 8.
+void check_xcd_order() {
+  for (int nwg = 1; nwg <= 2100; ++nwg) {
+    std::vector<char> seen(nwg, 0);
+    for (int i = 0; i < nwg; ++i) {
+      const int t = sgc::xcd_order(i, nwg);
+      CHECK(t >= 0 && t < nwg && !seen[t]);
+      if (t < 0 || t >= nwg) return;
+      seen[t] = 1;
+      if (i >= 8) CHECK(t == sgc::xcd_order(i - 8, nwg) + 1);
+    }
+  }
+  const int most = INT32_MAX;  // a wide grid holds at most this many workgroups
+  CHECK(sgc::xcd_order(0, most) == 0 && sgc::xcd_order(most - 1, most) < most);
+  CHECK(sgc::xcd_order(most - 1, most) == 6 * (most >> 3) + 6 + ((most - 1) >> 3));
+}
+
 // Where the 256-wide kernel splits A in registers, the tiles' pass over A counts:
 // a call of many rows and few columns keeps the 256-wide kernel, one whose pass
 // is short takes the tiles, and none takes tiles that it would not take on
@@ -431,6 +449,7 @@ int main(int argc, char** argv) {
   const bool picks = argc > 2 && std::strcmp(argv[1], "picks") == 0;
   check_validation();
   check_tile_rule();
+  check_xcd_order();
   check_split_in_rule();
   if (rule) check_tile_picks(argv[2]);
   if (picks) check_golden_picks(argv[2]);
