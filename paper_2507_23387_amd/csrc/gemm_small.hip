@@ -459,9 +459,9 @@ double grid_time(const GridCost& c, int64_t tiles, int64_t together, int64_t kst
 // where they come within 5 % of it (baseline: 10 %).  The constants (indexed by
 // Variant) are a least-squares fit to the kernels' times on 2335 problems per
 // order, from 16 to 16384 rows and columns at K = 64 to 16384
-// (profiles/tile_rule_grids.csv).  Over those the pick's GEMM is 0.6-1.0 % slower
+// (profiles/tile_rule_grids.csv).  Over those the pick's GEMM is 0.3-0.9 % slower
 // than the fastest tile's on average, and slower than the 256-wide kernels' by
-// more than 5 % on 12 of the 9340, at most 16 %.  Without `start` and the margin
+// more than 5 % on 2 of the 9340.  Without `start` and the margin
 // it was 1.6-3.4 %, and 231 problems ran up to 40 % slower than on the 256-wide
 // kernels, most of them where those fill a round or two at small K (termwise 1024
 // x 8192 x 512: 33-35 us on 128-wide tiles, 29-30).  What is left is mostly
@@ -526,11 +526,16 @@ int small_gemm_tile(int64_t M, int64_t N, int64_t K, int variant, bool unscaled,
   // Splitting A costs the 256-wide kernels 5 % (32768 x 256 x 1024 elementwise 76
   // us; a pass over A and 128-wide tiles 97; 8192 x 1024 x 1024 the other way, 74
   // and 64; termwise 16384 x 256 x 1024 42 and 47, 8192 x 256 x 4096 122 and 100).
-  if (split_us > 0) limit = std::min(limit, 1.05 * wide - split_us);
+  // On few workgroups the termwise kernel loses more (13632 x 1 x 16832: 614 us,
+  // 535 on tiles).
+  if (split_us > 0)
+    limit = std::min(limit, (variant == kTermwise ? 1.10 : 1.05) * wide - split_us);
   // Planes of A that the 256 MiB last-level cache cannot hold come back from HBM,
   // at the rate they went (27840 x 5 x 8832 elementwise: 496 us on the 256-wide
-  // kernel, 532 on 32-wide tiles).
-  const double read_us = 4.0 * M * K > 256.0 * (1 << 20) ? 0.5 * split_us : 0.0;
+  // kernel, 532 on 32-wide tiles).  Not termwise, whose 256 x 128 kernel splits a
+  // long A slower than that (13056 x 2 x 17920: 609 us, 540 on tiles).
+  const double read_us =
+      variant == kElementwise && 4.0 * M * K > 256.0 * (1 << 20) ? 0.5 * split_us : 0.0;
   int tile = 0;
   auto consider = [&](int side, double us) {
     us = std::max(us, read_us);

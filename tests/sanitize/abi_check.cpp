@@ -187,6 +187,8 @@ void check_split_in_rule() {
   CHECK(tile(16384, 512, 2048, sgc::kElementwise) == 0);
   CHECK(tile(16384, 256, 1024, sgc::kTermwise) == 0);
   CHECK(tile(27840, 5, 8832, sgc::kElementwise) == 0);  // planes past the last-level cache
+  CHECK(tile(13056, 2, 17920, sgc::kTermwise) != 0);
+  CHECK(tile(13632, 1, 16832, sgc::kTermwise) != 0);
   CHECK(tile(8192, 1024, 1024, sgc::kElementwise) != 0);
   CHECK(tile(8192, 256, 4096, sgc::kElementwise) != 0);
   CHECK(tile(8192, 256, 4096, sgc::kTermwise) != 0);
