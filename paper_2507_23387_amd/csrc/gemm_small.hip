@@ -470,7 +470,7 @@ double grid_time(const GridCost& c, int64_t tiles, int64_t together, int64_t kst
 // elementwise body, for s > 2^15: its folds make 64-wide tiles, of one wave per
 // SIMD, half again as slow (762 x 5771 x 2048: 105 us on them, 80 on 256 x 128);
 // with the others' constants 124 of 1666 problems ran more than 5 % slower than
-// on the 256-wide kernel, now 1.  A call whose range flag is set runs the same
+// on the 256-wide kernel, now none.  A call whose range flag is set runs the same
 // body on the tile picked for the scaled one.
 // Two workgroups of 32 or 64-wide tiles share a compute unit (64 KiB of LDS
 // each), so their rounds are of 512.  Where the lines lie for the elementwise
