@@ -139,6 +139,33 @@ def test_rows_and_columns_of_a_wide_problem(gpu, shape, kind):
     assert_parity(Wh, want, K, abs_ab(Ah, Bw), f"wide {kind} {shape}")
 
 
+@pytest.mark.parametrize("shape", [(298, 8200, 512), (190, 9001, 1000), (700, 30000, 192)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("order", ["elementwise", "termwise", "elementwise_cross_first", "hi_only"])
+def test_grids_of_consecutive_tiles_per_xcd(gpu, shape, order):
+    """A few rows of tiles against a B of more than 16 MiB, whose tiles are dealt
+    out to the XCDs in runs (grids that are no multiple of 8): bit for bit the
+    products with parts of B, which are below that size."""
+    import torch
+
+    from paper_2507_23387_amd import binding
+
+    M, N, K = shape
+    A, B = workloads.make_operands(M, N, K, M + K, "normal")
+    log(f"tiles per XCD {order} {M}x{N}x{K}")
+    dA, dB = to_dev(A), to_dev(B)
+
+    def call(b):
+        return binding.hgemm(dA, b) if order == "hi_only" else binding.matmul(dA, b, order=order)
+
+    C = call(dB)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(C).all())
+    for j in range(0, N, 2050):
+        part = call(dB[:, j:j + 2050].contiguous())
+        assert torch.equal(C[:, j:j + 2050].contiguous().view(torch.int32), part.view(torch.int32))
+
+
 @pytest.mark.parametrize("bit", ["clean", "all"])
 def test_report_of_a_wide_problem(gpu, bit):
     """The report without pre-scaling after a 256-wide GEMM: none and all of the
